@@ -85,12 +85,34 @@ template <class D> __host__ __device__ __forceinline__ D opq(D x) {
 #endif
   return x;
 }
+// The same for a lane index: addresses formed from it are formed again.
+__host__ __device__ __forceinline__ int opq_index(int x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" : "+v"(x));
+#endif
+  return x;
+}
 // Fence between amplitude terms: the instruction scheduler may not move work
 // across it, so the evaluation order chosen by the process compiler (which
 // keeps few currents live) is the order executed.
 __host__ __device__ __forceinline__ void term_fence() {
 #if defined(__HIP_DEVICE_COMPILE__)
   __builtin_amdgcn_sched_barrier(0);
+#endif
+}
+// term_fence that also ends the reuse of loaded values: what was read from
+// memory before it is read again after it instead of being held in registers.
+__host__ __device__ __forceinline__ void load_fence() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+#endif
+}
+// A value that has to be complete here: what feeds it is not deferred beyond
+// the fences that follow.
+template <class R> __host__ __device__ __forceinline__ void settle(cx<R>& x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" : "+v"(x.re), "+v"(x.im));
 #endif
 }
 // Hooks of the mixed path's cancellation guard (me_kernel.h), called by the

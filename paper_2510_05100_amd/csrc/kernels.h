@@ -91,4 +91,10 @@ RWGT_DECLARE_PROCESS(gg_ttgg)
 RWGT_DECLARE_PROCESS(gg_tttt)
 #undef RWGT_DECLARE_PROCESS
 
+// Double precision by the colour-ordered recursion (ordered.h); rows: only the
+// events rows[0 .. *nrows) (device), null: all.
+hipError_t launch_ordered_gg_ttgg(const double* soa, int64_t nevt, const CardPair* cards, int ncards,
+                                  const double* w_in, double* w_out, double* me_out, const int32_t* rows,
+                                  const unsigned int* nrows, hipStream_t s);
+
 }  // namespace rwgt

@@ -311,8 +311,21 @@ inline hipError_t launch_me_t(const double* soa, int64_t nevt, const CardPair* c
 }
 
 // Mixed precision with the cancellation guard: the float-amplitude kernel
-// flags the events whose kappa exceeds g.kmax (g.kmax < 0: none, kappa only),
-// then double precision re-evaluates the flagged events in place: one wave
+// flags the events whose kappa exceeds g.kmax (g.kmax < 0: none, kappa only).
+template <class PROC>
+inline hipError_t launch_me_flag_t(int precision, const double* soa, int64_t nevt, const CardPair* cards, int ncards,
+                                   const double* w_in, double* w_out, double* me_out, GuardArgs g, hipStream_t s) {
+  constexpr bool many = PROC::NCOL >= 8;
+  if (g.nflagged) hipLaunchKernelGGL(zero_count_kernel, dim3(1), dim3(1), 0, s, g.nflagged);
+  return precision == kPrecMixedBF16
+      ? launch_me_t<PROC, float, std::conditional_t<many, __bf16, void>, true>(soa, nevt, cards, ncards, w_in, w_out,
+                                                                               me_out, s, g)
+      : launch_me_t<PROC, float, std::conditional_t<many, _Float16, void>, true>(soa, nevt, cards, ncards, w_in,
+                                                                                 w_out, me_out, s, g);
+}
+inline bool reevaluates(const GuardArgs& g) { return !(g.kmax < 0.0) && g.flagged && g.nflagged; }
+
+// Then double precision re-evaluates the flagged events in place: one wave
 // per event and a lane per helicity for many-flow processes (me_wave_kernel),
 // else the one-lane-per-event kernel over the list (groups past the flagged
 // count leave at once).
@@ -320,14 +333,8 @@ template <class PROC>
 inline hipError_t launch_me_guarded_t(int precision, const double* soa, int64_t nevt, const CardPair* cards,
                                       int ncards, const double* w_in, double* w_out, double* me_out, GuardArgs g,
                                       hipStream_t s) {
-  constexpr bool many = PROC::NCOL >= 8;
-  if (g.nflagged) hipLaunchKernelGGL(zero_count_kernel, dim3(1), dim3(1), 0, s, g.nflagged);
-  hipError_t e = precision == kPrecMixedBF16
-      ? launch_me_t<PROC, float, std::conditional_t<many, __bf16, void>, true>(soa, nevt, cards, ncards, w_in, w_out,
-                                                                               me_out, s, g)
-      : launch_me_t<PROC, float, std::conditional_t<many, _Float16, void>, true>(soa, nevt, cards, ncards, w_in,
-                                                                                 w_out, me_out, s, g);
-  if (e != hipSuccess || g.kmax < 0.0 || !g.flagged || !g.nflagged) return e;
+  const hipError_t e = launch_me_flag_t<PROC>(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, g, s);
+  if (e != hipSuccess || !reevaluates(g)) return e;
   if constexpr (hel_split<PROC>() > 1) {
     const int64_t blocks = nevt < 4096 ? nevt : 4096;
     hipLaunchKernelGGL(me_wave_kernel<PROC>, dim3(unsigned(blocks)), dim3(64), 0, s, soa, nevt, cards, ncards, w_in,

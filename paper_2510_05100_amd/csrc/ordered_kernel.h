@@ -1,0 +1,163 @@
+// Device side of the colour-ordered recursion (ordered.h): half a wave per
+// event.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+#include "check.h"
+#include "kernels.h"
+#include "ordered.h"
+
+namespace rwgt {
+namespace ordered {
+
+// The shared currents of one event in LDS, component by component: eight
+// lanes that read eight neighbouring slots (or the same one) touch the 128
+// bytes of one LDS cycle.
+struct LdsMemory {
+  typedef double v2 __attribute__((ext_vector_type(2)));
+  struct Event {
+    v2 vec[4][kSlots];
+    v2 pol[2][8];
+    v2 mom[2][4];
+    double pol_u[8];
+  };
+  Event* s;
+  static __device__ __forceinline__ cx<double> c(v2 a) { return {a.x, a.y}; }
+  static __device__ __forceinline__ v2 r(cx<double> a) { return v2{a.re, a.im}; }
+  __device__ __forceinline__ LcK<double> mom(int g) const {
+    const v2 a = s->mom[0][g];
+    return {a.x, a.y, c(s->mom[1][g])};
+  }
+  __device__ __forceinline__ void set_mom(int g, const LcK<double>& k) {
+    s->mom[0][g] = v2{k.u, k.d};
+    s->mom[1][g] = r(k.p);
+  }
+  __device__ __forceinline__ Lc<double> pol(int i) const {      // u real, d = -u
+    const double u = s->pol_u[i];
+    return {{u, 0.0}, {-u, 0.0}, c(s->pol[0][i]), c(s->pol[1][i])};
+  }
+  __device__ __forceinline__ void set_pol(int i, const Lc<double>& v) {
+    s->pol_u[i] = v.u.re;
+    s->pol[0][i] = r(v.p);
+    s->pol[1][i] = r(v.m);
+  }
+  __device__ __forceinline__ Lc<double> vec(int i) const {
+    return {c(s->vec[0][i]), c(s->vec[1][i]), c(s->vec[2][i]), c(s->vec[3][i])};
+  }
+  __device__ __forceinline__ void set_vec(int i, const Lc<double>& v) {
+    s->vec[0][i] = r(v.u);
+    s->vec[1][i] = r(v.d);
+    s->vec[2][i] = r(v.p);
+    s->vec[3][i] = r(v.m);
+  }
+  __device__ __forceinline__ Spinor<double> spin(int i) const {
+    return {{c(s->vec[0][i]), c(s->vec[1][i]), c(s->vec[2][i]), c(s->vec[3][i])}};
+  }
+  __device__ __forceinline__ void set_spin(int i, const Spinor<double>& v) {
+#pragma unroll
+    for (int n = 0; n < 4; ++n) s->vec[n][i] = r(v.c[n]);
+  }
+};
+
+// Orders the LDS accesses of one wave (they execute in order; this keeps the
+// compiler from moving them across).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  load_fence();
+}
+
+// Momentum of particle a of event i.
+__device__ __forceinline__ void load_momentum(const double* soa, int64_t nevt, int npart, int a, int64_t i,
+                                              double (&p)[4]) {
+#pragma unroll
+  for (int mu = 0; mu < 4; ++mu) p[mu] = RWGT_AT(soa, int64_t(a * 4 + mu) * nevt + i, int64_t(npart) * 4 * nevt);
+}
+
+// Half a wave per event, one lane per evaluated helicity, under every card in
+// turn.  LISTED: the events rows[0 .. *nrows), workgroups striding over the
+// list; otherwise all nevt events, one workgroup per pair.
+//
+// Bound by the vector ALUs: they issue in 89 % of the cycles, 85 % of it FP64.
+// A wave evaluates a card of its two events in 6300 vector instructions, where
+// evaluating every diagram for every helicity takes about 5 times that.  Two
+// waves per SIMD (LDS 17 KB per wave, 256 registers, 33 spilled) hide the LDS
+// latency; the fences (load_fence, settle) hold the compiler to the order of
+// the source, without them it loads everything first and spills 1000
+// registers.  1e6 events, one new card: 12.9 - 14.4 ms (box to box; 75 ms
+// diagram by diagram, one lane per event and two waves splitting its
+// helicities), 777 events: 0.047 (2.4) ms.  A first form with two waves per 64
+// events and one lane per event shared the gluon currents only and needed 512
+// registers with 310 spilled, waiting in half of its cycles: 29.7 ms.
+template <class PROC, bool LISTED>
+__global__ __launch_bounds__(64, 2) void ordered_kernel(const double* __restrict__ soa, int64_t nevt,
+                                                        const CardPair* __restrict__ cards, int ncards,
+                                                        const double* __restrict__ w_in, double* __restrict__ w_out,
+                                                        double* __restrict__ me_out, const int32_t* __restrict__ rows,
+                                                        const unsigned int* __restrict__ nrows) {
+  __shared__ LdsMemory::Event mem[2];
+  const int t = int(threadIdx.x) & (kLanes - 1), half = int(threadIdx.x) / kLanes;
+  LdsMemory m{&mem[half]};
+  const int64_t n = LISTED ? int64_t(*nrows) : nevt;
+  int64_t first = int64_t(blockIdx.x) * 2;
+  if (LISTED && first >= n) return;
+  do {
+    const bool valid = first + half < n;
+    const int64_t r = valid ? first + half : n - 1;   // a missing second event repeats the last one
+    const int64_t i = LISTED ? int64_t(RWGT_AT(rows, r, nevt)) : r;
+    double pt[4], ptb[4];
+    if (LISTED) wave_sync();
+    {
+      const int g = t & 3;
+      double p[4];
+      load_momentum(soa, nevt, PROC::NPART, g < 2 ? g : g + 2, i, p);
+      m.set_mom(g, lc_momentum(p, g < 2 ? 1.0 : -1.0));
+    }
+    load_momentum(soa, nevt, PROC::NPART, 2, i, pt);
+    load_momentum(soa, nevt, PROC::NPART, 3, i, ptb);
+    double norm = 0.0;
+#pragma unroll 1
+    for (int k = 0; k < ncards; ++k) {
+      const Card<double>& cd = RWGT_AT(cards, k, ncards).d;
+      wave_sync();
+#pragma unroll
+      for (int mu = 0; mu < 4; ++mu) { pt[mu] = opq(pt[mu]); ptb[mu] = opq(ptb[mu]); }
+      double me = lane_me2(m, opq_index(t), pt, ptb, cd, [] { wave_sync(); }, [](const cx<double>(&f)[24]) {
+        return PROC::template colour_sum<double>(f);
+      });
+#pragma unroll
+      for (int d = 1; d < kLanes; d <<= 1) me += __shfl_xor(me, d);
+      me *= cd.gqq * cd.gqq * PROC::SCALE;
+      if (t != 0 || !valid) continue;
+      if (me_out) RWGT_AT(me_out, int64_t(k) * nevt + i, int64_t(ncards) * nevt) = me;
+      if (w_out) {
+        if (k == 0) {
+          norm = (me == 0.0 ? 0.0 : 1.0 / me) * RWGT_AT(w_in, i, nevt);
+        } else {
+          RWGT_AT(w_out, int64_t(k - 1) * nevt + i, int64_t(ncards - 1) * nevt) = norm * me;
+        }
+      }
+    }
+    first += int64_t(gridDim.x) * 2;
+  } while (LISTED && first < n);
+}
+
+// rows: at most nevt of them, counted on the device; 4096 workgroups keep
+// every SIMD at its two waves twice over.
+template <class PROC>
+inline hipError_t launch_ordered(const double* soa, int64_t nevt, const CardPair* cards, int ncards,
+                                 const double* w_in, double* w_out, double* me_out, const int32_t* rows,
+                                 const unsigned int* nrows, hipStream_t s) {
+  const int64_t pairs = (nevt + 1) / 2, blocks = rows && pairs > 4096 ? 4096 : pairs;
+  const auto kernel = rows ? ordered_kernel<PROC, true> : ordered_kernel<PROC, false>;
+  hipLaunchKernelGGL(kernel, dim3(unsigned(blocks)), dim3(64), 0, s, soa, nevt, cards, ncards, w_in, w_out, me_out,
+                     rows, nrows);
+  return hipGetLastError();
+}
+
+}  // namespace ordered
+}  // namespace rwgt
