@@ -113,11 +113,14 @@ int rwgt_eval(rwgt_ctx *ctx, const double *momenta, int64_t nevt, const double *
  * u u~ > e+ e- g every helicity amplitude factorises into a card-independent
  * kinematic part and F = A/s + B/(s - M_Z^2 + i M_Z Gamma_Z), with A and B
  * products of the two fermion lines' photon and Z couplings (B per chirality
- * class of the lines) and s the lepton pair's invariant mass; four probe
- * evaluations per event (Z couplings on one class) give the class weights,
- * then each card costs a few operations per event.  For g g > t t~ g g the
+ * class of the lines) and s the lepton pair's invariant mass; the class
+ * weights come once per event (mixed precision: from four probe evaluations
+ * with Z couplings on one class), then each card costs a few operations per
+ * event.  For g g > t t~ g g the
  * cards change alpha_s only and |M|^2 scales as alpha_s^4 (one evaluation).
- * Cost: 4 (or 1) matrix-element evaluations per event instead of 1 + nsets.
+ * Cost: one evaluation's kinematics per event (mixed precision: 4 evaluations)
+ * instead of 1 + nsets evaluations; in double precision rwgt_eval of the
+ * electroweak processes works the same way.
  * Errors as rwgt_eval. */
 int rwgt_eval_factored(rwgt_ctx *ctx, const double *momenta, int64_t nevt, const double *weights_in,
                        const double *param_sets, int32_t nsets, double *weights_out);
@@ -259,8 +262,8 @@ int rwgt_kernel_times(rwgt_ctx *ctx, float *ingest_ms, float *me_ms);
  * (DEVICE momenta [nevt][npart][4], weights in/out [nevt]) are reweighted from
  * the original card of contexts[ctx] to the card in params (HOST, one
  * param_sets row of that context's layout).  All segments of one call go to
- * one persistent kernel (workgroups take event tiles from a shared counter),
- * captured once into a HIP graph and replayed while the number of segments,
+ * one persistent kernel (its workgroups share out the event tiles), captured
+ * once into a HIP graph and replayed while the number of segments,
  * tiles and the schedule stay the same.  The schedule (tile size, workgroup
  * size, workgroups per CU, helicity split) comes from rwgt_batch_set_schedule,
  * the tuning cache written by rwgt_batch_tune, or a default.  The paper runs
@@ -297,7 +300,8 @@ int rwgt_batch_time(rwgt_batch *batch, float *ms);
  * of 64), persistent workgroups per compute unit, and hel_split: 0 = one lane
  * per event (both cards, every kept helicity), 1 = one lane per (event, card,
  * kept helicity), the lanes of an event added in the one-lane order (the
- * same result to the bit).  Errors: RWGT_EINVAL. */
+ * same result to the bit); in double precision, where an event's helicities
+ * share their work, both run one lane per event.  Errors: RWGT_EINVAL. */
 int rwgt_batch_set_schedule(rwgt_batch *batch, int32_t tile_events, int32_t block, int32_t blocks_per_cu,
                             int32_t hel_split);
 /* hel_split may be NULL. */

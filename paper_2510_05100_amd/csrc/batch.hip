@@ -5,10 +5,14 @@
 // and evaluate |M|^2 under the segment's original and new cards for each
 // event of the tile: w' = (w * (1/|M|^2_orig)) * |M|^2_new.  Momenta are read
 // in the caller's AoS layout ([nevt][npart][4]); no separate ingest pass.
+// Double precision evaluates the electroweak weights (electroweak.h) with one
+// lane per event; single precision the generated amplitudes, one lane per
+// event or (the helicity split) per event, card and helicity.
 #include <hip/hip_runtime.h>
 
 #include "batch.h"
 #include "check.h"
+#include "electroweak_kernel.h"
 #include "generated/gen_ee_mumu.h"
 #include "generated/gen_uu_eeg.h"
 #include "me_kernel.h"
@@ -142,6 +146,159 @@ __global__ __launch_bounds__(256) void batch_hel_kernel(const BatchSeg* __restri
   }
 }
 
+// w' of one event under two cards, as event_kernel computes it.
+template <int NPART>
+__device__ __forceinline__ double two_cards(const ew::Weights& w, const Card<double>& c0, const Card<double>& c1,
+                                            double average, double w_in) {
+  const double m0 = ew::me2<NPART>(w, c0, average), m1 = ew::me2<NPART>(w, c1, average);
+  return ((m0 == 0.0 ? 0.0 : 1.0 / m0) * w_in) * m1;
+}
+
+// The persistent kernel of the double-precision family.  Wave w of the launch's
+// n takes the tiles w, w + n, ... 64 events at a time; the words of the next
+// 64 are on their way while 64 are evaluated.  Tiles of one size cost the same
+// to within the two processes' difference, so dealing them out loses under a
+// tile per wave, where claiming them from one counter costs 16 ns each on this
+// chip whoever claims (4.0e6 events in 128 segments: 1050 us with 64-event
+// tiles, 297 us with 256).  Dealt out: 200 us with 256-event tiles, 650 MB, so
+// 3.2 TB/s (the diagrams of every helicity under both cards took 1.6 - 2.0
+// ms); two waves per SIMD at least, one took 236 us.
+struct Piece {
+  BatchSeg sg;                                 // wave-uniform
+  double cards;                                // word by lane: the original card, then the new one
+  int64_t e, e1;                               // the piece is the first 64 of events [e, e1) of the segment
+  __device__ __forceinline__ int count() const { return e1 - e < 64 ? int(e1 - e) : 64; }
+};
+struct Words { double mom[20], w_in; };        // what a lane fetches of a piece
+
+// p[i] of n for a pointer that was itself read from memory and is known to be
+// to global memory: as a generic (flat) access the load would count as an LDS
+// access too, and every wait for LDS would wait for it.
+__device__ __forceinline__ double load_global(const double* p, unsigned i, int64_t n) {
+  if constexpr (kBoundsChecked) return RWGT_AT(p, i, n);
+  else return ((const __attribute__((address_space(1))) double*)p)[i];
+}
+__device__ __forceinline__ void store_global(double* p, unsigned i, int64_t n, double v) {
+  if constexpr (kBoundsChecked) RWGT_AT(p, i, n) = v;
+  else ((__attribute__((address_space(1))) double*)p)[i] = v;
+}
+
+// Lane j's value in scalar registers.
+__device__ __forceinline__ int64_t lane_value(int64_t x, int j) {
+  const unsigned lo = unsigned(__builtin_amdgcn_readlane(int(x), j));
+  return int64_t((static_cast<unsigned long long>(unsigned(__builtin_amdgcn_readlane(int(x >> 32), j))) << 32) | lo);
+}
+__device__ __forceinline__ double lane_value(double x, int j) {
+  return __builtin_bit_cast(double, lane_value(__builtin_bit_cast(int64_t, x), j));
+}
+
+constexpr int kCardWords = int(sizeof(Card<double>) / 8);
+__device__ __forceinline__ Card<double> lane_card(double words, int first) {
+  Card<double> c;
+  double* f = reinterpret_cast<double*>(&c);
+#pragma unroll
+  for (int k = 0; k < kCardWords; ++k) f[k] = lane_value(words, first + k);
+  return c;
+}
+
+// The piece a tile starts with.  Its segment is the last one with tile0 <=
+// tile, searched with 64 candidates per step: two dependent reads for up to
+// 4096 segments, where halving the range takes twelve.  The segment's entry
+// and its two cards are read one word per lane and handed out with readlane
+// (as uniform reads they would take 60 vector registers: the tables might
+// change under the outputs' stores for all the compiler knows).
+__device__ __forceinline__ Piece locate(const BatchSeg* __restrict__ segs, int nseg, int tile_events,
+                                        const CardPair* __restrict__ cards, int64_t tile) {
+  const int lane = int(threadIdx.x & 63);
+  int lo = 0, n = nseg;                        // the segment is one of [lo, lo + n)
+  while (n > 1) {
+    const int step = (n + 63) / 64, j = lane * step;
+    const bool below = j < n && RWGT_AT(segs, lo + (j < n ? j : 0), nseg).tile0 <= tile;
+    const int at = (__popcll(__ballot(below)) - 1) * step;
+    lo += at;
+    n = n - at < step ? n - at : step;
+  }
+  lo = __builtin_amdgcn_readfirstlane(lo);
+  constexpr int kSegWords = int(sizeof(BatchSeg) / 8);
+  static_assert(kSegWords == 6 && 2 * kCardWords <= 64, "one word per lane");
+  const int64_t sw = RWGT_AT(reinterpret_cast<const int64_t*>(segs), int64_t(lo) * kSegWords + lane % kSegWords,
+                             int64_t(nseg) * kSegWords);
+  const CardPair& cp = RWGT_AT(cards, 2 * lo + (lane >= kCardWords && lane < 2 * kCardWords ? 1 : 0), 2 * nseg);
+  const double cw = reinterpret_cast<const double*>(&cp.d)[lane % kCardWords];
+  Piece p;
+  p.sg.proc = int32_t(lane_value(sw, 0));
+  p.sg.nevt = lane_value(sw, 1);
+  p.sg.tile0 = lane_value(sw, 2);
+  p.sg.mom = reinterpret_cast<const double*>(lane_value(sw, 3));
+  p.sg.w_in = reinterpret_cast<const double*>(lane_value(sw, 4));
+  p.sg.w_out = reinterpret_cast<double*>(lane_value(sw, 5));
+  p.cards = cw;
+  p.e = (tile - p.sg.tile0) * tile_events;
+  p.e1 = p.e + tile_events < p.sg.nevt ? p.e + tile_events : p.sg.nevt;
+  return p;
+}
+
+// As ew::fetch, for either process.
+__device__ __forceinline__ void fetch_piece(const Piece& p, Words& x) {
+  const int n = p.count(), width = p.sg.proc == 0 ? 16 : 20;
+  const unsigned lane = threadIdx.x & 63, last = unsigned(n * width - 1);
+  // uniform bases, so that a lane's addresses are 32-bit offsets
+  const double *w_in = p.sg.w_in + p.e, *mom = p.sg.mom + p.e * width;
+  const int64_t left = p.sg.nevt - p.e;
+  x.w_in = load_global(w_in, int(lane) < n ? lane : unsigned(n - 1), left);
+  auto words = [&](auto at) {
+#pragma unroll
+    for (int j = 0; j < 16; ++j) x.mom[j] = load_global(mom, at(lane + 64 * j), left * width);
+    if (width == 20) {
+#pragma unroll
+      for (int j = 16; j < 20; ++j) x.mom[j] = load_global(mom, at(lane + 64 * j), left * width);
+    }
+  };
+  if (n == 64) words([](unsigned t) { return t; });
+  else words([=](unsigned t) { return t < last ? t : last; });
+}
+
+template <int NPART>
+__device__ __forceinline__ double evaluate_piece(const double (&P)[5][4], const Piece& p, double w_in, double average) {
+  const double (&q)[NPART][4] = reinterpret_cast<const double (&)[NPART][4]>(P);
+  return two_cards<NPART>(ew::Process<NPART>::template weights<false>(q), lane_card(p.cards, 0),
+                          lane_card(p.cards, kCardWords), average, w_in);
+}
+
+__global__ __launch_bounds__(256, 2) void batch_ew_kernel(const BatchSeg* __restrict__ segs, int nseg, int64_t ntiles,
+                                                       int tile_events, const CardPair* __restrict__ cards) {
+  __shared__ union { ew::Tile<4> a; ew::Tile<5> b; } tiles[4];
+  auto& tile = tiles[threadIdx.x >> 6];
+  const int64_t waves = int64_t(gridDim.x) * (blockDim.x >> 6);
+  int64_t t = int64_t(blockIdx.x) * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+  if (t >= ntiles) return;                     // no barrier below: each wave ends by itself
+  Piece cur = locate(segs, nseg, tile_events, cards, t);
+  Words x;
+  fetch_piece(cur, x);
+  for (bool more = true; more;) {
+    Piece next = cur;
+    next.e += 64;
+    if (next.e >= next.e1) {
+      t += waves;
+      more = t < ntiles;
+      if (more) next = locate(segs, nseg, tile_events, cards, t);
+    }
+    double P[5][4];
+    const bool two = cur.sg.proc == 0;
+    const int n = cur.count();
+    if (two)
+      ew::spread<4>(tile.a, reinterpret_cast<const double (&)[16]>(x.mom), n, reinterpret_cast<double (&)[4][4]>(P));
+    else
+      ew::spread<5>(tile.b, x.mom, n, P);
+    const double w_in = x.w_in;
+    if (more) fetch_piece(next, x);
+    const double w = two ? evaluate_piece<4>(P, cur, w_in, gen_ee_mumu::AVERAGE)
+                         : evaluate_piece<5>(P, cur, w_in, gen_uu_eeg::AVERAGE);
+    if (int(threadIdx.x & 63) < n) store_global(cur.sg.w_out + cur.e, threadIdx.x & 63, cur.sg.nevt - cur.e, w);
+    cur = next;
+  }
+}
+
 template <class R, class... PROCS>
 static hipError_t launch_batch_t(const BatchSeg* segs, int nseg, int64_t ntiles, const BatchSchedule& sc,
                                  const CardPair* cards, unsigned long long* counter, hipStream_t s) {
@@ -224,11 +381,13 @@ hipError_t launch_exact_list(int family, int precision, int proc, const double* 
 hipError_t launch_batch(int family, int precision, const BatchSeg* segs, int nseg, int64_t ntiles,
                         const BatchSchedule& sc, const CardPair* cards, unsigned long long* counter,
                         hipStream_t s) {
-  const bool f64 = precision == kPrecFP64;
-  if (family == kFamilyElectroweak)
-    return f64 ? launch_batch_t<double, Proc_ee_mumu, Proc_uu_eeg>(segs, nseg, ntiles, sc, cards, counter, s)
-               : launch_batch_t<float, Proc_ee_mumu, Proc_uu_eeg>(segs, nseg, ntiles, sc, cards, counter, s);
-  return hipErrorInvalidValue;
+  if (family != kFamilyElectroweak) return hipErrorInvalidValue;
+  if (precision != kPrecFP64)
+    return launch_batch_t<float, Proc_ee_mumu, Proc_uu_eeg>(segs, nseg, ntiles, sc, cards, counter, s);
+  // one lane per event under either setting of the helicity split: an event
+  // is 400 FP64 instructions and has no helicity loop to split
+  hipLaunchKernelGGL(batch_ew_kernel, dim3(sc.grid), dim3(sc.block), 0, s, segs, nseg, ntiles, sc.tile_events, cards);
+  return hipGetLastError();
 }
 
 }  // namespace rwgt

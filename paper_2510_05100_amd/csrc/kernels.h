@@ -9,6 +9,15 @@
 
 namespace rwgt {
 
+// Orders the LDS accesses of one wave between lanes (they execute in order;
+// this keeps the compiler from moving them across).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  load_fence();
+}
+
 enum { kProcEeMumu = 0, kProcUuEeg = 1, kProcGgTtgg = 2, kProcGgTttt = 3 };
 enum { kPrecFP64 = 0, kPrecMixedFP16 = 1, kPrecMixedBF16 = 2 };
 constexpr int kMeBlock = 256;
@@ -18,8 +27,17 @@ hipError_t launch_ingest(int npart, const double* aos, double* soa, int64_t nevt
 // cards[0..ncards): |M|^2 per card -> me_out[k][nevt] (if non-null); when
 // w_out is non-null, card 0 is the original card and
 // w_out[k-1][i] = (w_in[i] * (1/|M|^2_0)) * |M|^2_k for k >= 1.
-hipError_t launch_me(int proc, int precision, const double* soa, int64_t nevt, const CardPair* cards, int ncards,
+// mom: the caller's [nevt][npart][4] where me_reads_aos, else [npart * 4][nevt].
+bool me_reads_aos(int proc, int precision);
+hipError_t launch_me(int proc, int precision, const double* mom, int64_t nevt, const CardPair* cards, int ncards,
                      const double* w_in, double* w_out, double* me_out, hipStream_t s);
+
+// The electroweak processes in double precision for a scan of cards: w_out as
+// launch_me, the lepton pair's mass squared as twice a product (electroweak.h).
+hipError_t launch_scan_ee_mumu(const double* mom, int64_t nevt, const CardPair* cards, int ncards, const double* w_in,
+                               double* w_out, hipStream_t s);
+hipError_t launch_scan_uu_eeg(const double* mom, int64_t nevt, const CardPair* cards, int ncards, const double* w_in,
+                              double* w_out, hipStream_t s);
 
 // Default threshold of the mixed path's cancellation guard: measured on 4e6
 // g g -> t t~ g g events (FP16 colour sum), it re-evaluates 0.10 % of them and
@@ -39,7 +57,8 @@ struct GuardArgs {
 
 // Mixed-precision |M|^2 / w' (precision RWGT_MIXED_*) with the events whose
 // cancellation measure exceeds g.kmax re-evaluated in double precision.
-hipError_t launch_me_guarded(int proc, int precision, const double* soa, int64_t nevt, const CardPair* cards,
+// soa: [npart * 4][nevt], mom: the same momenta as [nevt][npart][4].
+hipError_t launch_me_guarded(int proc, int precision, const double* soa, const double* mom, int64_t nevt, const CardPair* cards,
                              int ncards, const double* w_in, double* w_out, double* me_out, const GuardArgs& g,
                              hipStream_t s);
 
@@ -78,11 +97,11 @@ void process_constants(int proc, int* npart, int* ngood, int* ncol, int* ndiag);
 double process_flops(int proc, bool executed);
 
 #define RWGT_DECLARE_PROCESS(NAME)                                                                        \
-  hipError_t launch_me_##NAME(int precision, const double* soa, int64_t nevt, const CardPair* cards,     \
+  hipError_t launch_me_##NAME(int precision, const double* mom, int64_t nevt, const CardPair* cards,     \
                               int ncards, const double* w_in, double* w_out, double* me_out, hipStream_t s); \
-  hipError_t launch_me_guarded_##NAME(int precision, const double* soa, int64_t nevt, const CardPair* cards, \
-                                      int ncards, const double* w_in, double* w_out, double* me_out,          \
-                                      const GuardArgs& g, hipStream_t s);                                     \
+  hipError_t launch_me_guarded_##NAME(int precision, const double* soa, const double* mom, int64_t nevt,  \
+                                      const CardPair* cards, int ncards, const double* w_in,             \
+                                      double* w_out, double* me_out, const GuardArgs& g, hipStream_t s);  \
   void constants_##NAME(int* npart, int* ngood, int* ncol, int* ndiag);                                 \
   double flops_##NAME(bool executed);
 RWGT_DECLARE_PROCESS(ee_mumu)
@@ -93,7 +112,7 @@ RWGT_DECLARE_PROCESS(gg_tttt)
 
 // Double precision by the colour-ordered recursion (ordered.h); rows: only the
 // events rows[0 .. *nrows) (device), null: all.
-hipError_t launch_ordered_gg_ttgg(const double* soa, int64_t nevt, const CardPair* cards, int ncards,
+hipError_t launch_ordered_gg_ttgg(const double* mom, int64_t nevt, const CardPair* cards, int ncards,
                                   const double* w_in, double* w_out, double* me_out, const int32_t* rows,
                                   const unsigned int* nrows, hipStream_t s);
 

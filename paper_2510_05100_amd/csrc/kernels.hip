@@ -288,27 +288,32 @@ hipError_t launch_ingest(int npart, const double* aos, double* soa, int64_t nevt
   return hipGetLastError();
 }
 
-hipError_t launch_me(int proc, int precision, const double* soa, int64_t nevt, const CardPair* cards, int ncards,
+// The double-precision kernels read the caller's layout, except four tops.
+bool me_reads_aos(int proc, int precision) { return precision == kPrecFP64 && proc != kProcGgTttt; }
+
+hipError_t launch_me(int proc, int precision, const double* mom, int64_t nevt, const CardPair* cards, int ncards,
                      const double* w_in, double* w_out, double* me_out, hipStream_t s) {
   switch (proc) {
-    case kProcEeMumu: return launch_me_ee_mumu(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, s);
-    case kProcUuEeg: return launch_me_uu_eeg(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, s);
-    case kProcGgTtgg: return launch_me_gg_ttgg(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, s);
-    case kProcGgTttt: return launch_me_gg_tttt(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, s);
+    case kProcEeMumu: return launch_me_ee_mumu(precision, mom, nevt, cards, ncards, w_in, w_out, me_out, s);
+    case kProcUuEeg: return launch_me_uu_eeg(precision, mom, nevt, cards, ncards, w_in, w_out, me_out, s);
+    case kProcGgTtgg: return launch_me_gg_ttgg(precision, mom, nevt, cards, ncards, w_in, w_out, me_out, s);
+    case kProcGgTttt: return launch_me_gg_tttt(precision, mom, nevt, cards, ncards, w_in, w_out, me_out, s);
   }
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_me_guarded(int proc, int precision, const double* soa, int64_t nevt, const CardPair* cards,
-                             int ncards, const double* w_in, double* w_out, double* me_out, const GuardArgs& g,
+hipError_t launch_me_guarded(int proc, int precision, const double* soa, const double* mom, int64_t nevt,
+                             const CardPair* cards, int ncards, const double* w_in, double* w_out, double* me_out, const GuardArgs& g,
                              hipStream_t s) {
   switch (proc) {
-    case kProcEeMumu: return launch_me_guarded_ee_mumu(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, g, s);
-    case kProcUuEeg: return launch_me_guarded_uu_eeg(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, g, s);
+    case kProcEeMumu:
+      return launch_me_guarded_ee_mumu(precision, soa, mom, nevt, cards, ncards, w_in, w_out, me_out, g, s);
+    case kProcUuEeg:
+      return launch_me_guarded_uu_eeg(precision, soa, mom, nevt, cards, ncards, w_in, w_out, me_out, g, s);
     case kProcGgTtgg:
-      return launch_me_guarded_gg_ttgg(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, g, s);
+      return launch_me_guarded_gg_ttgg(precision, soa, mom, nevt, cards, ncards, w_in, w_out, me_out, g, s);
     case kProcGgTttt:
-      return launch_me_guarded_gg_tttt(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, g, s);
+      return launch_me_guarded_gg_tttt(precision, soa, mom, nevt, cards, ncards, w_in, w_out, me_out, g, s);
   }
   return hipErrorInvalidValue;
 }

@@ -7,6 +7,7 @@
 #include <cstdint>
 
 #include "check.h"
+#include "helas.h"
 #include "kernels.h"
 #include "ordered.h"
 
@@ -62,20 +63,11 @@ struct LdsMemory {
   }
 };
 
-// Orders the LDS accesses of one wave (they execute in order; this keeps the
-// compiler from moving them across).
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  load_fence();
-}
-
-// Momentum of particle a of event i.
-__device__ __forceinline__ void load_momentum(const double* soa, int64_t nevt, int npart, int a, int64_t i,
+// Momentum of particle a of event i, in the caller's layout.
+__device__ __forceinline__ void load_momentum(const double* mom, int64_t nevt, int npart, int a, int64_t i,
                                               double (&p)[4]) {
 #pragma unroll
-  for (int mu = 0; mu < 4; ++mu) p[mu] = RWGT_AT(soa, int64_t(a * 4 + mu) * nevt + i, int64_t(npart) * 4 * nevt);
+  for (int mu = 0; mu < 4; ++mu) p[mu] = RWGT_AT(mom, (i * npart + a) * 4 + mu, nevt * npart * 4);
 }
 
 // Half a wave per event, one lane per evaluated helicity, under every card in
@@ -94,7 +86,7 @@ __device__ __forceinline__ void load_momentum(const double* soa, int64_t nevt, i
 // events and one lane per event shared the gluon currents only and needed 512
 // registers with 310 spilled, waiting in half of its cycles: 29.7 ms.
 template <class PROC, bool LISTED>
-__global__ __launch_bounds__(64, 2) void ordered_kernel(const double* __restrict__ soa, int64_t nevt,
+__global__ __launch_bounds__(64, 2) void ordered_kernel(const double* __restrict__ mom, int64_t nevt,
                                                         const CardPair* __restrict__ cards, int ncards,
                                                         const double* __restrict__ w_in, double* __restrict__ w_out,
                                                         double* __restrict__ me_out, const int32_t* __restrict__ rows,
@@ -114,11 +106,11 @@ __global__ __launch_bounds__(64, 2) void ordered_kernel(const double* __restrict
     {
       const int g = t & 3;
       double p[4];
-      load_momentum(soa, nevt, PROC::NPART, g < 2 ? g : g + 2, i, p);
+      load_momentum(mom, nevt, PROC::NPART, g < 2 ? g : g + 2, i, p);
       m.set_mom(g, lc_momentum(p, g < 2 ? 1.0 : -1.0));
     }
-    load_momentum(soa, nevt, PROC::NPART, 2, i, pt);
-    load_momentum(soa, nevt, PROC::NPART, 3, i, ptb);
+    load_momentum(mom, nevt, PROC::NPART, 2, i, pt);
+    load_momentum(mom, nevt, PROC::NPART, 3, i, ptb);
     double norm = 0.0;
 #pragma unroll 1
     for (int k = 0; k < ncards; ++k) {
@@ -149,12 +141,12 @@ __global__ __launch_bounds__(64, 2) void ordered_kernel(const double* __restrict
 // rows: at most nevt of them, counted on the device; 4096 workgroups keep
 // every SIMD at its two waves twice over.
 template <class PROC>
-inline hipError_t launch_ordered(const double* soa, int64_t nevt, const CardPair* cards, int ncards,
+inline hipError_t launch_ordered(const double* mom, int64_t nevt, const CardPair* cards, int ncards,
                                  const double* w_in, double* w_out, double* me_out, const int32_t* rows,
                                  const unsigned int* nrows, hipStream_t s) {
   const int64_t pairs = (nevt + 1) / 2, blocks = rows && pairs > 4096 ? 4096 : pairs;
   const auto kernel = rows ? ordered_kernel<PROC, true> : ordered_kernel<PROC, false>;
-  hipLaunchKernelGGL(kernel, dim3(unsigned(blocks)), dim3(64), 0, s, soa, nevt, cards, ncards, w_in, w_out, me_out,
+  hipLaunchKernelGGL(kernel, dim3(unsigned(blocks)), dim3(64), 0, s, mom, nevt, cards, ncards, w_in, w_out, me_out,
                      rows, nrows);
   return hipGetLastError();
 }

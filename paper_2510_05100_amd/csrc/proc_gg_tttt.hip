@@ -7,13 +7,13 @@ namespace rwgt {
 
 RWGT_PROCESS_TRAITS(gg_tttt)
 
-hipError_t launch_me_gg_tttt(int precision, const double* soa, int64_t nevt, const CardPair* cards, int ncards,
+hipError_t launch_me_gg_tttt(int precision, const double* mom, int64_t nevt, const CardPair* cards, int ncards,
                             const double* w_in, double* w_out, double* me_out, hipStream_t s) {
-  return launch_me_prec<Proc_gg_tttt>(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, s);
+  return launch_me_prec<Proc_gg_tttt>(precision, mom, nevt, cards, ncards, w_in, w_out, me_out, s);
 }
 
-hipError_t launch_me_guarded_gg_tttt(int precision, const double* soa, int64_t nevt, const CardPair* cards,
-                                    int ncards, const double* w_in, double* w_out, double* me_out,
+hipError_t launch_me_guarded_gg_tttt(int precision, const double* soa, const double* mom, int64_t nevt,
+                                    const CardPair* cards, int ncards, const double* w_in, double* w_out, double* me_out,
                                     const GuardArgs& g, hipStream_t s) {
   return launch_me_guarded_t<Proc_gg_tttt>(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, g, s);
 }

@@ -229,7 +229,7 @@ struct rwgt_ctx {
 namespace {
 
 int ensure_buffers(rwgt_ctx* c, int64_t nevt, int ncards) {
-  if (nevt > c->soa_events) {
+  if (!rwgt::me_reads_aos(c->def->id, c->precision) && nevt > c->soa_events) {
     if (c->soa) {
       hipStreamSynchronize(c->stream);
       hipFree(c->soa);
@@ -293,7 +293,8 @@ int ensure_guard(rwgt_ctx* c, int64_t nevt) {
 }
 
 int run(rwgt_ctx* c, bool reweight, const double* momenta, int64_t nevt, const double* w_in,
-        const double* param_sets, int32_t nsets, double* w_out, double* me_out, double* kappa_out = nullptr) {
+        const double* param_sets, int32_t nsets, double* w_out, double* me_out, double* kappa_out = nullptr,
+        bool ew_scan = false) {
   if (nevt < 0) return c->fail(RWGT_EINVAL, "nevt < 0");
   if (nsets < 1) return c->fail(RWGT_EINVAL, "nsets < 1");
   if (!param_sets) return c->fail(RWGT_EINVAL, "param_sets is NULL");
@@ -321,8 +322,11 @@ int run(rwgt_ctx* c, bool reweight, const double* momenta, int64_t nevt, const d
   if (e != hipSuccess) return c->hip_fail(e, "hipEventRecord");
   c->upload_pending = true;
   if (c->profiling) hipEventRecord(c->ev[0], c->stream);
-  e = rwgt::launch_ingest(c->def->npart, momenta, c->soa, nevt, c->stream);
-  if (e != hipSuccess) return c->hip_fail(e, "ingest kernel");
+  const bool aos = rwgt::me_reads_aos(c->def->id, c->precision);
+  if (!aos) {
+    e = rwgt::launch_ingest(c->def->npart, momenta, c->soa, nevt, c->stream);
+    if (e != hipSuccess) return c->hip_fail(e, "ingest kernel");
+  }
   if (c->profiling) hipEventRecord(c->ev[1], c->stream);
   c->guard_ran = false;
   if (c->precision != RWGT_FP64 && (kappa_out || c->guard_kmax > 0.0)) {
@@ -338,11 +342,14 @@ int run(rwgt_ctx* c, bool reweight, const double* momenta, int64_t nevt, const d
       g.nflagged = c->guard_count;
       c->guard_ran = true;
     }
-    e = rwgt::launch_me_guarded(c->def->id, c->precision, c->soa, nevt, c->dcards, int(cards.size()), w_in, w_out,
-                                me_out, g, c->stream);
+    e = rwgt::launch_me_guarded(c->def->id, c->precision, c->soa, momenta, nevt, c->dcards, int(cards.size()), w_in,
+                                w_out, me_out, g, c->stream);
+  } else if (ew_scan) {
+    e = (c->def->id == rwgt::kProcEeMumu ? rwgt::launch_scan_ee_mumu : rwgt::launch_scan_uu_eeg)(
+        momenta, nevt, c->dcards, int(cards.size()), w_in, w_out, c->stream);
   } else {
-    e = rwgt::launch_me(c->def->id, c->precision, c->soa, nevt, c->dcards, int(cards.size()), w_in, w_out, me_out,
-                        c->stream);
+    e = rwgt::launch_me(c->def->id, c->precision, aos ? momenta : c->soa, nevt, c->dcards, int(cards.size()), w_in,
+                        w_out, me_out, c->stream);
   }
   if (e != hipSuccess) return c->hip_fail(e, "matrix-element kernel");
   if (c->profiling) hipEventRecord(c->ev[2], c->stream);
@@ -590,6 +597,11 @@ int rwgt_eval_factored(rwgt_ctx* c, const double* momenta, int64_t nevt, const d
   if (nsets < 1) return c->fail(RWGT_EINVAL, "nsets < 1");
   if (!param_sets) return c->fail(RWGT_EINVAL, "param_sets is NULL");
   try {
+    if (c->precision == RWGT_FP64 && (c->def->id == rwgt::kProcEeMumu || c->def->id == rwgt::kProcUuEeg)) {
+      // the double-precision electroweak kernel is factored itself: each event's weights once, then every card
+      const int done = run(c, true, momenta, nevt, w_in, param_sets, nsets, w_out, nullptr, nullptr, true);
+      return done == RWGT_OK ? count_nonfinite(c, w_out, int64_t(nsets) * nevt) : done;
+    }
     std::vector<CardPair> cards;
     int rc = build_cards(c, param_sets, nsets, true, cards);
     if (rc != RWGT_OK) return rc;
@@ -668,10 +680,11 @@ int rwgt_eval_factored(rwgt_ctx* c, const double* momenta, int64_t nevt, const d
                        c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return c->hip_fail(e, "factor card upload");
-    e = rwgt::launch_ingest(c->def->npart, momenta, c->soa, nevt, c->stream);
+    const bool aos = rwgt::me_reads_aos(id, c->precision);
+    if (!aos) e = rwgt::launch_ingest(c->def->npart, momenta, c->soa, nevt, c->stream);
     if (e == hipSuccess)
-      e = rwgt::launch_me(id, c->precision, c->soa, nevt, c->dcards, nprobe, nullptr, nullptr, c->fac_probe,
-                          c->stream);
+      e = rwgt::launch_me(id, c->precision, aos ? momenta : c->soa, nevt, c->dcards, nprobe, nullptr, nullptr,
+                          c->fac_probe, c->stream);
     if (e == hipSuccess)
       e = rwgt::launch_factored(ew, c->soa, c->def->npart, nevt, ia, ib, c->fac_probe, o.mz, o.wz, c->fac_cards,
                                 int(fc.size()), w_in, w_out, c->stream);
