@@ -63,7 +63,9 @@ hipError_t launch_me_guarded(int proc, int precision, const double* soa, const d
                              hipStream_t s);
 
 // Reweighted cross sections and errors per card: out[k] = {sigma', dsigma', fallback flag};
-// part must hold nsets * (3 * nblocks + 3) doubles (two-pass scratch).
+// at most nblocks workgroups per card, xsec_blocks of them: part must hold
+// nsets * 3 * xsec_blocks(nevt, nblocks) doubles.
+int xsec_blocks(int64_t nevt, int nblocks);
 hipError_t launch_xsec(const double* w_in, const double* w_out, int64_t nevt, int nsets, double sigma, double dsigma,
                        double norm, double* part, int nblocks, double* out, hipStream_t s);
 

@@ -195,6 +195,10 @@ struct rwgt_ctx {
   // rwgt_me2): momenta, then weights in, then outputs
   double* stage = nullptr;
   size_t stage_bytes = 0;
+  // cross sections: block partials and (pinned) results
+  double* xsec_part = nullptr;
+  double* xsec_host = nullptr;
+  size_t xsec_bytes = 0, xsec_host_bytes = 0;
   // non-finite outputs of the last evaluation: per-block counts on the device
   unsigned long long* nf_part = nullptr;
   unsigned long long* nf_host = nullptr;   // pinned
@@ -220,8 +224,10 @@ struct rwgt_ctx {
     for (void* p : {sur_x, static_cast<void*>(sur_list), static_cast<void*>(sur_count), static_cast<void*>(sur_heads),
                     static_cast<void*>(sur_cards), static_cast<void*>(sur_cpar), static_cast<void*>(fac_probe),
                     static_cast<void*>(fac_cards), static_cast<void*>(as_cards), static_cast<void*>(nf_part),
-                    static_cast<void*>(guard_list), static_cast<void*>(guard_count), static_cast<void*>(stage)})
+                    static_cast<void*>(guard_list), static_cast<void*>(guard_count), static_cast<void*>(stage),
+                    static_cast<void*>(xsec_part)})
       if (p) hipFree(p);
+    if (xsec_host) hipHostFree(xsec_host);
     if (nf_host) hipHostFree(nf_host);
   }
 };
@@ -884,18 +890,44 @@ int rwgt_xsec(rwgt_ctx* ctx, const double* weights_in, const double* weights_out
   ctx->err.clear();
   if (nevt < 1 || nsets < 1 || !weights_in || !weights_out || !xsec || !xerr)
     return ctx->fail(RWGT_EINVAL, "bad arguments");
+  // Partial sums on the device and results in pinned memory, which the last
+  // kernel writes itself: kept by the context up to kKeep (allocating, copying
+  // back and freeing them took 40 us of a 64-card call), the call's own beyond.
   constexpr int kBlocks = 512;
-  double *part = nullptr, *out = nullptr;
+  constexpr size_t kKeep = size_t(16) << 20;
+  const size_t pbytes = size_t(nsets) * 3 * size_t(rwgt::xsec_blocks(nevt, kBlocks)) * sizeof(double);
+  const size_t rbytes = size_t(nsets) * 3 * sizeof(double);
+  const bool keep = pbytes <= kKeep;
+  double *part = nullptr, *host = nullptr;
   hipError_t e = hipSetDevice(ctx->device);
-  if (e == hipSuccess) e = hipMalloc(&part, size_t(nsets) * (3 * kBlocks + 3) * sizeof(double));
-  if (e == hipSuccess) e = hipMalloc(&out, size_t(nsets) * 3 * sizeof(double));
+  if (keep && e == hipSuccess && (pbytes > ctx->xsec_bytes || rbytes > ctx->xsec_host_bytes)) {
+    e = hipStreamSynchronize(ctx->stream);
+    if (ctx->xsec_part) (void)hipFree(ctx->xsec_part);
+    if (ctx->xsec_host) (void)hipHostFree(ctx->xsec_host);
+    ctx->xsec_part = ctx->xsec_host = nullptr;
+    const size_t pb = std::max(pbytes, ctx->xsec_bytes), rb = std::max(rbytes, ctx->xsec_host_bytes);
+    ctx->xsec_bytes = ctx->xsec_host_bytes = 0;
+    if (e == hipSuccess) e = hipMalloc(&ctx->xsec_part, pb);
+    if (e == hipSuccess) e = hipHostMalloc(&ctx->xsec_host, rb, hipHostMallocDefault);
+    if (e == hipSuccess) { ctx->xsec_bytes = pb; ctx->xsec_host_bytes = rb; }
+  }
+  if (!keep) {
+    if (e == hipSuccess) e = hipMalloc(&part, pbytes);
+    if (e == hipSuccess) e = hipHostMalloc(&host, rbytes, hipHostMallocDefault);
+  } else {
+    part = ctx->xsec_part;
+    host = ctx->xsec_host;
+  }
   if (e == hipSuccess)
-    e = rwgt::launch_xsec(weights_in, weights_out, nevt, nsets, sigma, dsigma, norm, part, kBlocks, out, ctx->stream);
-  std::vector<double> host(size_t(nsets) * 3);
-  if (e == hipSuccess) e = hipMemcpyAsync(host.data(), out, host.size() * sizeof(double), hipMemcpyDeviceToHost, ctx->stream);
+    e = rwgt::launch_xsec(weights_in, weights_out, nevt, nsets, sigma, dsigma, norm, part, kBlocks, host, ctx->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-  if (part) hipFree(part);
-  if (out) hipFree(out);
+  struct Scratch {                              // of a call too large for the kept workspace
+    double *part, *host;
+    ~Scratch() {
+      if (part) (void)hipFree(part);
+      if (host) (void)hipHostFree(host);
+    }
+  } scratch{keep ? nullptr : part, keep ? nullptr : host};
   if (e != hipSuccess) return ctx->hip_fail(e, "cross-section reduction");
   for (int32_t k = 0; k < nsets; ++k) {
     xsec[k] = host[k * 3];
@@ -911,8 +943,7 @@ int rwgt_xsec(rwgt_ctx* ctx, const double* weights_in, const double* weights_out
 }  // extern "C"
 
 // ------------------------------------------------ rwgt_xsec without allocation
-// Scratch of rwgt_xsec_noalloc: the two passes' block partials and the
-// per-card sums and results for up to kXsecStaticSets cards, in a static
+// Scratch of rwgt_xsec_noalloc: the block partials and the results for up to kXsecStaticSets cards, in a static
 // device array (each GPU holds its own copy until the process ends).  Host
 // code reaches it only through the address hipGetSymbolAddress returns on
 // that device (the array's name is a host-side stand-in there).
