@@ -30,8 +30,6 @@ namespace ew {
 
 #pragma clang fp contract(off)
 
-#define RWGT_HD __host__ __device__ __forceinline__
-
 typedef cx<double> C;
 RWGT_HD double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 RWGT_HD C mul(C a, C b) { return {fma_(-a.im, b.im, a.re * b.re), fma_(a.im, b.re, a.re * b.im)}; }
@@ -164,7 +162,6 @@ template <int NPART> RWGT_HD double me2(const Weights& w, const Card<double>& cd
   return sum * (average * P::kColour * P::coupling(cd));
 }
 
-#undef RWGT_HD
 #pragma clang fp contract(fast)
 }  // namespace ew
 }  // namespace rwgt

@@ -46,7 +46,6 @@ __host__ __device__ __forceinline__ void jamps(const D (&P)[4][4], int hel, cons
   for (int c = 0; c < NCOL; ++c) jamp[c] = cx<R>{R(0), R(0)};
   note_reset(jamp);
   cx<R> amp;
-  {  // group 1
   const D pw3[4] = {opq(P[3][0]), opq(P[3][1]), opq(P[3][2]), opq(P[3][3])};
   const Spinor<R> w3 = oxx<R>(pw3, Massless{}, h3, 1);
   const D pw2[4] = {opq(P[2][0]), opq(P[2][1]), opq(P[2][2]), opq(P[2][3])};
@@ -67,43 +66,6 @@ __host__ __device__ __forceinline__ void jamps(const D (&P)[4][4], int hel, cons
   jamp[0] = jamp[0] + amp;
   note_amp(jamp, amp, 1);
   term_fence();
-  }
-}
-
-// Same amplitudes with the terms in 1 group(s), currents rebuilt in each
-// group: fewer live registers (used for the double-precision kernel).
-// Routine counts per helicity: ixx 2, oxx 2, vxx 0, ffv_in 0, ffv_out 0, ffv_vec0 1, ffv_vecm 1, vvv_vec 0, vvvv_vec 0, ffv_amp 2, pair_w 0
-template <class R, class D, class J>
-__host__ __device__ __forceinline__ void jamps_grouped(const D (&P)[4][4], int hel, const Card<R, D>& cd, J& jamp) {
-  const int h0 = ((hel >> 3) & 1) ? 1 : -1;
-  const int h1 = ((hel >> 2) & 1) ? 1 : -1;
-  const int h2 = ((hel >> 1) & 1) ? 1 : -1;
-  const int h3 = ((hel >> 0) & 1) ? 1 : -1;
-  for (int c = 0; c < NCOL; ++c) jamp[c] = cx<R>{R(0), R(0)};
-  note_reset(jamp);
-  cx<R> amp;
-  {  // group 1
-  const D pw3[4] = {opq(P[3][0]), opq(P[3][1]), opq(P[3][2]), opq(P[3][3])};
-  const Spinor<R> w3 = oxx<R>(pw3, Massless{}, h3, 1);
-  const D pw2[4] = {opq(P[2][0]), opq(P[2][1]), opq(P[2][2]), opq(P[2][3])};
-  const Spinor<R> w2 = ixx<R>(pw2, Massless{}, h2, -1);
-  const D q1[4] = {-opq(P[2][0]) - opq(P[3][0]), -opq(P[2][1]) - opq(P[3][1]), -opq(P[2][2]) - opq(P[3][2]), -opq(P[2][3]) - opq(P[3][3])};
-  const Vec<R> v2 = ffv_vec0_v<R>(w3, w2, cd.a[1], q1);
-  const D pw0[4] = {opq(P[0][0]), opq(P[0][1]), opq(P[0][2]), opq(P[0][3])};
-  const Spinor<R> w0 = oxx<R>(pw0, Massless{}, h0, -1);
-  const D pw1[4] = {opq(P[1][0]), opq(P[1][1]), opq(P[1][2]), opq(P[1][3])};
-  const Spinor<R> w1 = ixx<R>(pw1, Massless{}, h1, 1);
-  amp = ffv_amp_v<R>(w0, w1, v2, cd.a[0]);
-  jamp[0] = jamp[0] + amp;
-  note_amp(jamp, amp, 1);
-  term_fence();
-  const D q3[4] = {-opq(P[2][0]) - opq(P[3][0]), -opq(P[2][1]) - opq(P[3][1]), -opq(P[2][2]) - opq(P[3][2]), -opq(P[2][3]) - opq(P[3][3])};
-  const Vec<R> v4 = ffv_vecm_c<R>(w3, w2, cd.zL[1], cd.zR[1], q3, cd.mz, cd.wz);
-  amp = ffv_amp_c<R>(w0, w1, v4, cd.zL[0], cd.zR[0]);
-  jamp[0] = jamp[0] + amp;
-  note_amp(jamp, amp, 1);
-  term_fence();
-  }
 }
 
 template <class R, class J>

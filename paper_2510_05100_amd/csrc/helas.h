@@ -25,6 +25,8 @@
 
 #include <type_traits>
 
+#define RWGT_HD __host__ __device__ __forceinline__
+
 namespace rwgt {
 
 // Mass argument of a massless line: the mass terms are dropped at compile

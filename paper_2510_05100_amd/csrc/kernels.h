@@ -47,8 +47,6 @@ constexpr double kGuardKappaDefault = 300.0;
 
 // Cancellation guard of the mixed path (me_kernel.h, launch_me_guarded).
 struct GuardArgs {
-  const int32_t* rows = nullptr;          // re-evaluation: the event of each row
-  const unsigned int* nrows = nullptr;    // re-evaluation: number of rows (device)
   int32_t* flagged = nullptr;             // guard: events to re-evaluate (capacity nevt)
   unsigned int* nflagged = nullptr;       // guard: their count (device)
   double kmax = 0.0;                      // guard: kappa above this is flagged (< 0: flag nothing)
@@ -112,9 +110,12 @@ RWGT_DECLARE_PROCESS(gg_ttgg)
 RWGT_DECLARE_PROCESS(gg_tttt)
 #undef RWGT_DECLARE_PROCESS
 
-// Double precision by the colour-ordered recursion (ordered.h); rows: only the
-// events rows[0 .. *nrows) (device), null: all.
+// Double precision by the colour-ordered recursions (ordered.h, ordered_pairs.h);
+// rows: only the events rows[0 .. *nrows) (device), null: all.
 hipError_t launch_ordered_gg_ttgg(const double* mom, int64_t nevt, const CardPair* cards, int ncards,
+                                  const double* w_in, double* w_out, double* me_out, const int32_t* rows,
+                                  const unsigned int* nrows, hipStream_t s);
+hipError_t launch_ordered_gg_tttt(const double* mom, int64_t nevt, const CardPair* cards, int ncards,
                                   const double* w_in, double* w_out, double* me_out, const int32_t* rows,
                                   const unsigned int* nrows, hipStream_t s);
 

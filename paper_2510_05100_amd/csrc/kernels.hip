@@ -303,8 +303,8 @@ hipError_t launch_ingest(int npart, const double* aos, double* soa, int64_t nevt
   return hipGetLastError();
 }
 
-// The double-precision kernels read the caller's layout, except four tops.
-bool me_reads_aos(int proc, int precision) { return precision == kPrecFP64 && proc != kProcGgTttt; }
+// The double-precision kernels read the caller's layout.
+bool me_reads_aos(int, int precision) { return precision == kPrecFP64; }
 
 hipError_t launch_me(int proc, int precision, const double* mom, int64_t nevt, const CardPair* cards, int ncards,
                      const double* w_in, double* w_out, double* me_out, hipStream_t s) {

@@ -1,5 +1,5 @@
-// Device side of the colour-ordered recursion (ordered.h): half a wave per
-// event.
+// Device side of the colour-ordered recursions (ordered.h, ordered_pairs.h):
+// half a wave per event.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -10,6 +10,7 @@
 #include "helas.h"
 #include "kernels.h"
 #include "ordered.h"
+#include "ordered_pairs.h"
 
 namespace rwgt {
 namespace ordered {
@@ -17,13 +18,14 @@ namespace ordered {
 // The shared currents of one event in LDS, component by component: eight
 // lanes that read eight neighbouring slots (or the same one) touch the 128
 // bytes of one LDS cycle.
+template <int SLOTS, int POLS, int MOMENTA>
 struct LdsMemory {
   typedef double v2 __attribute__((ext_vector_type(2)));
   struct Event {
-    v2 vec[4][kSlots];
-    v2 pol[2][8];
-    v2 mom[2][4];
-    double pol_u[8];
+    v2 vec[4][SLOTS];
+    v2 pol[2][POLS];
+    v2 mom[2][MOMENTA];
+    double pol_u[(POLS + 1) / 2 * 2];
   };
   Event* s;
   static __device__ __forceinline__ cx<double> c(v2 a) { return {a.x, a.y}; }
@@ -70,30 +72,66 @@ __device__ __forceinline__ void load_momentum(const double* mom, int64_t nevt, i
   for (int mu = 0; mu < 4; ++mu) p[mu] = RWGT_AT(mom, (i * npart + a) * 4 + mu, nevt * npart * 4);
 }
 
+// The recursions: their memory, the momenta it starts with, and a lane's part.
+struct QuarkLine {                               // g g -> Q Q~ g g
+  typedef LdsMemory<kSlots, kPols, 4> Memory;
+  static __device__ __forceinline__ void fill(Memory& m, int t, const double* mom, int64_t nevt, int64_t i) {
+    const int g = t & 3;                         // gluons: particles 0, 1 in, 4, 5 out
+    double p[4];
+    load_momentum(mom, nevt, 6, g < 2 ? g : g + 2, i, p);
+    m.set_mom(g, lc_momentum(p, g < 2 ? 1.0 : -1.0));
+  }
+  template <class Colour>
+  static __device__ __forceinline__ double lane(Memory& m, int t, const double* mom, int64_t nevt, int64_t i,
+                                                const Card<double>& cd, Colour colour) {
+    double pt[4], ptb[4];
+    load_momentum(mom, nevt, 6, 2, i, pt);
+    load_momentum(mom, nevt, 6, 3, i, ptb);
+    return lane_me2(m, t, pt, ptb, cd, [] { wave_sync(); }, colour);
+  }
+};
+struct QuarkPairs {                              // g g -> Q Q~ Q Q~
+  typedef LdsMemory<pairs::kSlots, pairs::kPols, 6> Memory;
+  static __device__ __forceinline__ void fill(Memory& m, int t, const double* mom, int64_t nevt, int64_t i) {
+    const int a = t < 6 ? t : 5;
+    double p[4];
+    load_momentum(mom, nevt, 6, a, i, p);
+    m.set_mom(a, lc_momentum(p, 1.0));
+  }
+  template <class Colour>
+  static __device__ __forceinline__ double lane(Memory& m, int t, const double* mom, int64_t nevt, int64_t i,
+                                                const Card<double>& cd, Colour colour) {
+    auto load = [&](int a, double (&p)[4]) { load_momentum(mom, nevt, 6, a, i, p); };
+    return pairs::lane_me2(m, t, load, cd, [] { wave_sync(); }, colour);
+  }
+};
+
 // Half a wave per event, one lane per evaluated helicity, under every card in
 // turn.  LISTED: the events rows[0 .. *nrows), workgroups striding over the
 // list; otherwise all nevt events, one workgroup per pair.
 //
 // Bound by the vector ALUs: they issue in 89 % of the cycles, 85 % of it FP64.
 // A wave evaluates a card of its two events in 6300 vector instructions, where
-// evaluating every diagram for every helicity takes about 5 times that.  Two
-// waves per SIMD (LDS 17 KB per wave, 256 registers, 33 spilled) hide the LDS
-// latency; the fences (load_fence, settle) hold the compiler to the order of
-// the source, without them it loads everything first and spills 1000
-// registers.  1e6 events, one new card: 12.9 - 14.4 ms (box to box; 75 ms
-// diagram by diagram, one lane per event and two waves splitting its
-// helicities), 777 events: 0.047 (2.4) ms.  A first form with two waves per 64
+// evaluating every diagram for every helicity takes about 5 times that
+// (g g -> t t~ g g; g g -> t t~ t t~ 4 times).  Two waves per SIMD (LDS 17 KB
+// per wave, 256 registers, 25 spilled; 164, none) hide the LDS latency; the
+// fences (load_fence, settle) hold the compiler to the order of the source,
+// without them it loads everything first and spills 1000 registers.  1e6
+// events, one new card: 12.5 - 14.4 ms (from card to card; 75 ms diagram by
+// diagram, one lane per event and two waves splitting its helicities), 777
+// events: 0.043 (2.4) ms; g g -> t t~ t t~, 250001 events: 2.48 (9.32) ms.  A
+// first form for g g -> t t~ g g with two waves per 64
 // events and one lane per event shared the gluon currents only and needed 512
 // registers with 310 spilled, waiting in half of its cycles: 29.7 ms.
-template <class PROC, bool LISTED>
+template <class PROC, class REC, bool LISTED>
 __global__ __launch_bounds__(64, 2) void ordered_kernel(const double* __restrict__ mom, int64_t nevt,
                                                         const CardPair* __restrict__ cards, int ncards,
                                                         const double* __restrict__ w_in, double* __restrict__ w_out,
                                                         double* __restrict__ me_out, const int32_t* __restrict__ rows,
                                                         const unsigned int* __restrict__ nrows) {
-  __shared__ LdsMemory::Event mem[2];
+  __shared__ typename REC::Memory::Event mem[2];
   const int t = int(threadIdx.x) & (kLanes - 1), half = int(threadIdx.x) / kLanes;
-  LdsMemory m{&mem[half]};
+  typename REC::Memory m{&mem[half]};
   const int64_t n = LISTED ? int64_t(*nrows) : nevt;
   int64_t first = int64_t(blockIdx.x) * 2;
   if (LISTED && first >= n) return;
@@ -101,24 +139,14 @@ __global__ __launch_bounds__(64, 2) void ordered_kernel(const double* __restrict
     const bool valid = first + half < n;
     const int64_t r = valid ? first + half : n - 1;   // a missing second event repeats the last one
     const int64_t i = LISTED ? int64_t(RWGT_AT(rows, r, nevt)) : r;
-    double pt[4], ptb[4];
     if (LISTED) wave_sync();
-    {
-      const int g = t & 3;
-      double p[4];
-      load_momentum(mom, nevt, PROC::NPART, g < 2 ? g : g + 2, i, p);
-      m.set_mom(g, lc_momentum(p, g < 2 ? 1.0 : -1.0));
-    }
-    load_momentum(mom, nevt, PROC::NPART, 2, i, pt);
-    load_momentum(mom, nevt, PROC::NPART, 3, i, ptb);
+    REC::fill(m, t, mom, nevt, i);
     double norm = 0.0;
 #pragma unroll 1
     for (int k = 0; k < ncards; ++k) {
       const Card<double>& cd = RWGT_AT(cards, k, ncards).d;
       wave_sync();
-#pragma unroll
-      for (int mu = 0; mu < 4; ++mu) { pt[mu] = opq(pt[mu]); ptb[mu] = opq(ptb[mu]); }
-      double me = lane_me2(m, opq_index(t), pt, ptb, cd, [] { wave_sync(); }, [](const cx<double>(&f)[24]) {
+      double me = REC::lane(m, opq_index(t), mom, nevt, i, cd, [](const cx<double>(&f)[PROC::NCOL]) {
         return PROC::template colour_sum<double>(f);
       });
 #pragma unroll
@@ -140,12 +168,12 @@ __global__ __launch_bounds__(64, 2) void ordered_kernel(const double* __restrict
 
 // rows: at most nevt of them, counted on the device; 4096 workgroups keep
 // every SIMD at its two waves twice over.
-template <class PROC>
+template <class PROC, class REC>
 inline hipError_t launch_ordered(const double* mom, int64_t nevt, const CardPair* cards, int ncards,
                                  const double* w_in, double* w_out, double* me_out, const int32_t* rows,
                                  const unsigned int* nrows, hipStream_t s) {
   const int64_t pairs = (nevt + 1) / 2, blocks = rows && pairs > 4096 ? 4096 : pairs;
-  const auto kernel = rows ? ordered_kernel<PROC, true> : ordered_kernel<PROC, false>;
+  const auto kernel = rows ? ordered_kernel<PROC, REC, true> : ordered_kernel<PROC, REC, false>;
   hipLaunchKernelGGL(kernel, dim3(unsigned(blocks)), dim3(64), 0, s, mom, nevt, cards, ncards, w_in, w_out, me_out,
                      rows, nrows);
   return hipGetLastError();

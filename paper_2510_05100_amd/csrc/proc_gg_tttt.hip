@@ -9,13 +9,17 @@ RWGT_PROCESS_TRAITS(gg_tttt)
 
 hipError_t launch_me_gg_tttt(int precision, const double* mom, int64_t nevt, const CardPair* cards, int ncards,
                             const double* w_in, double* w_out, double* me_out, hipStream_t s) {
+  if (precision == kPrecFP64)
+    return launch_ordered_gg_tttt(mom, nevt, cards, ncards, w_in, w_out, me_out, nullptr, nullptr, s);
   return launch_me_prec<Proc_gg_tttt>(precision, mom, nevt, cards, ncards, w_in, w_out, me_out, s);
 }
 
 hipError_t launch_me_guarded_gg_tttt(int precision, const double* soa, const double* mom, int64_t nevt,
                                     const CardPair* cards, int ncards, const double* w_in, double* w_out, double* me_out,
                                     const GuardArgs& g, hipStream_t s) {
-  return launch_me_guarded_t<Proc_gg_tttt>(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, g, s);
+  const hipError_t e = launch_me_flag_t<Proc_gg_tttt>(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, g, s);
+  if (e != hipSuccess || !reevaluates(g)) return e;
+  return launch_ordered_gg_tttt(mom, nevt, cards, ncards, w_in, w_out, me_out, g.flagged, g.nflagged, s);
 }
 
 void constants_gg_tttt(int* npart, int* ngood, int* ncol, int* ndiag) {

@@ -90,8 +90,6 @@ class Emitter:
                       "ffv_vecm": 0, "vvv_vec": 0, "vvvv_vec": 0, "ffv_amp": 0, "pair_w": 0}
         self.n = 0
         self.two = d.term_lines is not None
-        self.fence_every = 1                     # a scheduling fence after every k-th term
-        self.nterms = 0
         self.line = (d.bleg.idx, d.fleg.idx)     # main line of the amplitude being emitted
 
     def lkey(self, kind, seq, line):
@@ -298,9 +296,7 @@ class Emitter:
                 expr = f"amp * cx<R>{{R({re}), R({im})}}"
             self.emit(f"jamp[{idx}] = jamp[{idx}] + {expr};")
         self.emit(f"note_amp(jamp, amp, {len(colour)});")
-        self.nterms += 1
-        if self.nterms % self.fence_every == 0:
-            self.emit("term_fence();")
+        self.emit("term_fence();")
 
 
 def colour_matrix_ints(d: Diagrams):
@@ -538,45 +534,23 @@ def refine_order(order, term_nodes, iters=30000, seed=20251005):
     return best
 
 
-# Groups of amplitude terms per helicity.  Between groups every current is
-# forgotten and rebuilt on demand (from opaque momentum reads, so nothing is
-# carried across): fewer currents live at once for some recomputation.
-GROUPS = {"gg_ttgg": 3, "gg_tttt": 2}
-# Terms between scheduling fences in the grouped (double-precision) body: the
-# scheduler may interleave the terms of one span; a fence after every term
-# and no fence at all both measured slower for g g -> t t~ g g.
-FENCE_EVERY = {"gg_ttgg": 20, "gg_tttt": 4}
-
-
-def emit_body(d: Diagrams, groups: int, fence_every: int = 1):
-    """Statements of the amplitude code with the terms split into groups."""
+def emit_body(d: Diagrams):
+    """Statements of the amplitude code, term by term in the scheduled order."""
     em = Emitter(d)
-    em.fence_every = fence_every
     splits, shared = plan_splits(d)
-    order = schedule(em, splits, shared)
-    cuts = {round(g * len(order) / groups) for g in range(1, groups)}
-    em.emit("{  // group 1")
-    for pos, t in enumerate(order):
-        if pos in cuts:
-            em.cache.clear()
-            em.emit("}")
-            em.emit("term_fence();")
-            em.emit("{  // next group: currents are rebuilt from here on")
+    for t in schedule(em, splits, shared):
         seq, colour = d.terms[t]
         em.line = term_line(d, t)
         em.amplitude(seq, colour, splits[t], shared[t])
-    em.emit("}")
     return em
 
 
-def generate(d: Diagrams, groups: int | None = None) -> str:
+def generate(d: Diagrams) -> str:
     name = d.process.name
     legs = d.process.legs
     n = len(legs)
-    em = emit_body(d, 1)
+    em = emit_body(d)
     body = em.lines
-    groups = groups or GROUPS.get(d.process.name, 1)
-    em_g = emit_body(d, groups, FENCE_EVERY.get(d.process.name, 1)) if groups > 1 else em
     num, den = colour_matrix_ints(d)
     good, nsum, helw = summed_helicities(d, good_helicities(d))
     ncol = len(d.basis)
@@ -631,19 +605,6 @@ def generate(d: Diagrams, groups: int | None = None) -> str:
     out.append("  note_reset(jamp);")
     out.append("  cx<R> amp;")
     out.extend(body)
-    out.append("}")
-    out.append("")
-    out.append(f"// Same amplitudes with the terms in {groups} group(s), currents rebuilt in each")
-    out.append("// group: fewer live registers (used for the double-precision kernel).")
-    out.append("// Routine counts per helicity: " + ", ".join(f"{k} {v}" for k, v in em_g.count.items()))
-    out.append("template <class R, class D, class J>")
-    out.append(f"__host__ __device__ __forceinline__ void jamps_grouped(const D (&P)[{n}][4], int hel, const Card<R, D>& cd, J& jamp) {{")
-    for i in range(n):
-        out.append(f"  const int h{i} = ((hel >> {n - 1 - i}) & 1) ? 1 : -1;")
-    out.append("  for (int c = 0; c < NCOL; ++c) jamp[c] = cx<R>{R(0), R(0)};")
-    out.append("  note_reset(jamp);")
-    out.append("  cx<R> amp;")
-    out.extend(em_g.lines)
     out.append("}")
     out.append("")
     # colour sum: J^dagger C J = sum_i J_i^* (C J)_i, C real symmetric

@@ -1,5 +1,6 @@
-// The colour-ordered recursion of g g -> t t~ g g (ordered.h) on the host in
-// double precision, one thread per lane: |M|^2 per event.
+// The colour-ordered recursions of g g -> t t~ g g (ordered.h) and, built with
+// -DPAIRS, of g g -> t t~ t t~ (ordered_pairs.h) on the host in double
+// precision, one thread per lane: |M|^2 per event.
 //   stdin:  n alpha_s m_t, then n lines of 6 x 4 momenta (E px py pz)
 //   stdout: n values of |M|^2
 #include <hip/hip_runtime.h>
@@ -11,14 +12,22 @@
 #include <thread>
 #include <vector>
 
+#ifdef PAIRS
+#include "generated/gen_gg_tttt.h"
+#include "ordered_pairs.h"
+namespace gen = rwgt::gen_gg_tttt;
+using namespace rwgt::ordered::pairs;
+#else
 #include "generated/gen_gg_ttgg.h"
 #include "ordered.h"
+namespace gen = rwgt::gen_gg_ttgg;
+#endif
 
 using namespace rwgt;
 using namespace rwgt::ordered;
 
 struct Memory {
-  LcK<double> k[4];
+  LcK<double> k[6];
   Lc<double> p[kPols];
   cx<double> v[kSlots][4];
   LcK<double> mom(int g) const { return k[g]; }
@@ -42,26 +51,38 @@ int main() {
   cd.g4 = cd.g3 * cd.g3;
   cd.mt = mt;
   std::vector<Memory> mem(static_cast<size_t>(n));
-  static const int particle[4] = {0, 1, 4, 5};
-  for (int e = 0; e < n; ++e)
-    for (int g = 0; g < 4; ++g) mem[size_t(e)].k[g] = lc_momentum(&P[size_t(e * 24 + particle[g] * 4)], g < 2 ? 1.0 : -1.0);
+  for (int e = 0; e < n; ++e) {
+    const double* p = &P[size_t(e * 24)];
+#ifdef PAIRS
+    for (int a = 0; a < 6; ++a) mem[size_t(e)].k[a] = lc_momentum(p + 4 * a, 1.0);
+#else
+    static const int particle[4] = {0, 1, 4, 5};
+    for (int g = 0; g < 4; ++g) mem[size_t(e)].k[g] = lc_momentum(p + 4 * particle[g], g < 2 ? 1.0 : -1.0);
+#endif
+  }
   pthread_barrier_t bar;
-  pthread_barrier_init(&bar, nullptr, kLanes);
-  std::vector<double> part(size_t(n) * kLanes);
+  pthread_barrier_init(&bar, nullptr, 32);
+  std::vector<double> part(size_t(n) * 32);
   std::vector<std::thread> lanes;
-  for (int t = 0; t < kLanes; ++t)
+  for (int t = 0; t < 32; ++t)
     lanes.emplace_back([&, t] {
-      for (int e = 0; e < n; ++e)
-        part[size_t(e * kLanes + t)] =
-            lane_me2(mem[size_t(e)], t, &P[size_t(e * 24 + 8)], &P[size_t(e * 24 + 12)], cd,
-                     [&] { pthread_barrier_wait(&bar); },
-                     [](const cx<double>(&f)[24]) { return gen_gg_ttgg::colour_sum<double>(f); });
+      auto sync = [&] { pthread_barrier_wait(&bar); };
+      auto colour = [](const cx<double>(&f)[gen::NCOL]) { return gen::colour_sum<double>(f); };
+      for (int e = 0; e < n; ++e) {
+        const double* p = &P[size_t(e * 24)];
+#ifdef PAIRS
+        auto load = [&](int a, double (&q)[4]) { for (int m = 0; m < 4; ++m) q[m] = p[4 * a + m]; };
+        part[size_t(e * 32 + t)] = pairs::lane_me2(mem[size_t(e)], t, load, cd, sync, colour);
+#else
+        part[size_t(e * 32 + t)] = lane_me2(mem[size_t(e)], t, p + 8, p + 12, cd, sync, colour);
+#endif
+      }
     });
   for (auto& l : lanes) l.join();
   for (int e = 0; e < n; ++e) {
     double me = 0.0;
-    for (int t = 0; t < kLanes; ++t) me += part[size_t(e * kLanes + t)];
-    std::printf("%.17g\n", me * cd.gqq * cd.gqq * gen_gg_ttgg::AVERAGE * gen_gg_ttgg::HELW);
+    for (int t = 0; t < 32; ++t) me += part[size_t(e * 32 + t)];
+    std::printf("%.17g\n", me * cd.gqq * cd.gqq * gen::AVERAGE * gen::HELW);
   }
   return 0;
 }

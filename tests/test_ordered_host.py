@@ -1,10 +1,10 @@
-"""The colour-ordered recursion of the double-precision g g -> t t~ g g kernel
-(csrc/ordered.h), compiled for the host with one thread per lane
+"""The colour-ordered recursions of the double-precision kernels of
+g g -> t t~ g g (csrc/ordered.h) and g g -> t t~ t t~ (csrc/ordered_pairs.h), compiled for the host with one thread per lane
 (tests/host/ordered_me.cpp), against the oracle: the tasks' index arithmetic,
 the relations between orderings and the vertices, without a GPU.
 
 1e-12 relative, the bar of the generated code on the host: both sides are
-double-precision sums of the same 24 flows in different orders.
+double-precision sums of the same flows (24, 12) in different orders.
 """
 import os
 import shutil
@@ -19,17 +19,21 @@ from oracle import reweight
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-@pytest.fixture(scope="module")
-def exe(tmp_path_factory):
+def _build(tmp_path_factory, *flags):
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
     if not os.path.exists(hipcc):
         pytest.skip("hipcc not available")
     out = str(tmp_path_factory.mktemp("ordered") / "ordered_me")
-    cmd = [hipcc, "-O1", "-std=c++17", "-pthread", "-I" + os.path.join(ROOT, "paper_2510_05100_amd", "csrc"),
+    cmd = [hipcc, *flags, "-O1", "-std=c++17", "-pthread", "-I" + os.path.join(ROOT, "paper_2510_05100_amd", "csrc"),
            os.path.join(ROOT, "tests", "host", "ordered_me.cpp"), "-o", out]
     r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-3000:]
     return out
+
+
+@pytest.fixture(scope="module")
+def exe(tmp_path_factory):
+    return _build(tmp_path_factory)
 
 
 def _run(exe, p, card):
@@ -66,3 +70,10 @@ def test_gluons_along_the_beam(exe):
     q[:, 1, 1:] = q[:, 1, [3, 1, 2]]
     got, want = _run(exe, q[:4], synth.ORIG_QCD), reweight.me2("gg_ttgg", q[:4], synth.ORIG_QCD)
     np.testing.assert_allclose(got, want, rtol=1e-11)
+
+
+def test_pairs_on_host_against_oracle(tmp_path_factory):
+    pairs = _build(tmp_path_factory, "-DPAIRS")
+    p = synth.events("gg_tttt", 200)[::10]
+    for card in (synth.ORIG_QCD, synth.NEW_QCD):
+        np.testing.assert_allclose(_run(pairs, p, card), reweight.me2("gg_tttt", p, card), rtol=1e-12)
