@@ -21,6 +21,10 @@ struct Card {
   D mz, wz, mt;          // double on the device: resonant and mass terms
 };
 
+// What the double-precision QCD kernels read of a card.
+struct QcdCard { double gqq, g3, g4, mt; };
+inline __host__ __device__ QcdCard qcd_card(const Card<double>& c) { return {c.gqq, c.g3, c.g4, c.mt}; }
+
 // Both precisions of one card, filled on the host.
 struct CardPair {
   Card<double> d;

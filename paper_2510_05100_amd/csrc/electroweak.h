@@ -147,19 +147,30 @@ template <> struct Process<5> {                 // u(p0) u~(p1) -> e+(p2) e-(p3)
   }
 };
 
-// |M|^2 under one card; average: over initial spins and colours.
-template <int NPART> RWGT_HD double me2(const Weights& w, const Card<double>& cd, double average) {
+// What one card brings to |M|^2: the products of the lines' photon and Z
+// couplings, M_Z, M_Z Gamma_Z and the factor in front (average: over initial
+// spins and colours).
+struct Couplings { double a, ll, rr, lr, rl, mz, y, front; };
+template <int NPART> RWGT_HD Couplings couplings(const Card<double>& cd, double average) {
   typedef Process<NPART> P;
-  const double ga = (cd.a[P::kLine1] * cd.a[P::kLine2]) * w.inv_s;
-  const double x = fma_(-cd.mz, cd.mz, w.s), y = cd.mz * cd.wz, inv = quot(1.0, fma_(y, y, x * x));
-  const double gr = x * inv, gi = y * inv;
   const double l1 = cd.zL[P::kLine1], r1 = cd.zR[P::kLine1], l2 = cd.zL[P::kLine2], r2 = cd.zR[P::kLine2];
+  return {cd.a[P::kLine1] * cd.a[P::kLine2], l1 * l2, r1 * r2, l1 * r2, r1 * l2, cd.mz, cd.mz * cd.wz,
+          average * P::kColour * P::coupling(cd)};
+}
+// |M|^2 under one card.
+RWGT_HD double me2(const Weights& w, const Couplings& c) {
+  const double ga = c.a * w.inv_s;
+  const double x = fma_(-c.mz, c.mz, w.s), inv = quot(1.0, fma_(c.y, c.y, x * x));
+  const double gr = x * inv, gi = c.y * inv;
   auto f2 = [&](double b) {
     const double re = fma_(b, gr, ga), im = b * gi;
     return fma_(im, im, re * re);
   };
-  const double sum = fma_(w.same, f2(l1 * l2) + f2(r1 * r2), w.opp * (f2(l1 * r2) + f2(r1 * l2)));
-  return sum * (average * P::kColour * P::coupling(cd));
+  const double sum = fma_(w.same, f2(c.ll) + f2(c.rr), w.opp * (f2(c.lr) + f2(c.rl)));
+  return sum * c.front;
+}
+template <int NPART> RWGT_HD double me2(const Weights& w, const Card<double>& cd, double average) {
+  return me2(w, couplings<NPART>(cd, average));
 }
 
 #pragma clang fp contract(fast)

@@ -4,7 +4,9 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
+#include "card_source.h"
 #include "check.h"
 #include "electroweak.h"
 #include "kernels.h"
@@ -74,22 +76,28 @@ __device__ __forceinline__ void load_event(const double* __restrict__ mom, int64
 }
 
 // Every card of event i: |M|^2 and / or w' (card 0 is then the original).
-template <int NPART>
-__device__ __forceinline__ void all_cards(const Weights& w, const CardPair* __restrict__ cards, int ncards,
-                                          double average, int64_t i, int64_t nevt, double w_in,
-                                          double* __restrict__ w_out, double* __restrict__ me_out) {
+// Returns the number of non-finite w' (without w_out: |M|^2).
+template <class CARDS>
+__device__ __forceinline__ int all_cards(const Weights& w, const CARDS& cards, int ncards, int64_t i, int64_t nevt,
+                                         double w_in, double* __restrict__ w_out, double* __restrict__ me_out) {
   double norm = 0.0;
+  int bad = 0;
   for (int k = 0; k < ncards; ++k) {
-    const double me = me2<NPART>(w, RWGT_AT(cards, k, ncards).d, average);
+    const double me = me2(w, cards(k));
     if (me_out) RWGT_AT(me_out, int64_t(k) * nevt + i, int64_t(ncards) * nevt) = me;
     if (w_out) {
       if (k == 0) {
         norm = (me == 0.0 ? 0.0 : 1.0 / me) * w_in;
       } else {
-        RWGT_AT(w_out, int64_t(k - 1) * nevt + i, int64_t(ncards - 1) * nevt) = norm * me;
+        const double wk = norm * me;
+        RWGT_AT(w_out, int64_t(k - 1) * nevt + i, int64_t(ncards - 1) * nevt) = wk;
+        bad += isfinite(wk) ? 0 : 1;
       }
+    } else {
+      bad += isfinite(me) ? 0 : 1;
     }
   }
+  return bad;
 }
 
 // All events, straight from the caller's momenta (no ingest pass), one wave
@@ -100,11 +108,11 @@ __device__ __forceinline__ void all_cards(const Weights& w, const CardPair* __re
 // card: 45 us, 3.9 TB/s (ingest 52 us and the diagrams of 8 helicities under
 // both cards 640 us before; 65 us without the prefetch).
 // PRODUCT: see pair_mass.
-template <int NPART, bool PRODUCT>
-__global__ __launch_bounds__(64) void event_kernel(const double* __restrict__ mom, int64_t nevt,
-                                                   const CardPair* __restrict__ cards, int ncards, double average,
-                                                   const double* __restrict__ w_in, double* __restrict__ w_out,
-                                                   double* __restrict__ me_out) {
+template <int NPART, bool PRODUCT, class CARDS>
+__global__ __launch_bounds__(64) void event_kernel(const double* __restrict__ mom, int64_t nevt, const CARDS cards,
+                                                   int ncards, const double* __restrict__ w_in,
+                                                   double* __restrict__ w_out, double* __restrict__ me_out,
+                                                   unsigned long long* __restrict__ nonfinite) {
   __shared__ Tile<NPART> tile;
   const int lane = int(threadIdx.x);
   const int64_t stride = int64_t(gridDim.x) * 64;
@@ -116,6 +124,7 @@ __global__ __launch_bounds__(64) void event_kernel(const double* __restrict__ mo
     w_next = w_out ? RWGT_AT(w_in, first + (lane < n ? lane : n - 1), nevt) : 0.0;
     fetch<NPART>(mom, first, n, nevt, raw);
   };
+  int bad = 0;
   fetch_tile(e0);
   for (;;) {
     const int nloc = nevt - e0 < 64 ? int(nevt - e0) : 64;
@@ -125,11 +134,22 @@ __global__ __launch_bounds__(64) void event_kernel(const double* __restrict__ mo
     const double weight = w_next;
     if (next < nevt) fetch_tile(next);
     const Weights w = Process<NPART>::template weights<PRODUCT>(P);
-    if (lane < nloc) all_cards<NPART>(w, cards, ncards, average, e0 + lane, nevt, weight, w_out, me_out);
-    if (next >= nevt) return;
+    if (lane < nloc) bad += all_cards(w, cards, ncards, e0 + lane, nevt, weight, w_out, me_out);
+    if (next >= nevt) break;
     e0 = next;
   }
+  if (nonfinite) {
+    for (int d = 32; d > 0; d >>= 1) bad += __shfl_xor(bad, d);
+    if (lane == 0) RWGT_AT(nonfinite, blockIdx.x, gridDim.x) = static_cast<unsigned long long>(bad);
+  }
 }
+
+template <int NPART> struct PairCards {          // the mixed path's cards
+  const CardPair* p;
+  int n;
+  double average;
+  __device__ __forceinline__ Couplings operator()(int k) const { return couplings<NPART>(RWGT_AT(p, k, n).d, average); }
+};
 
 // The events rows[0 .. *nrows) (the mixed path's flagged ones).
 template <int NPART>
@@ -143,27 +163,42 @@ __global__ __launch_bounds__(64) void listed_kernel(const double* __restrict__ m
     const int64_t i = int64_t(RWGT_AT(rows, r, nevt));
     double P[NPART][4];
     load_event<NPART>(mom, i, nevt, P);
-    all_cards<NPART>(Process<NPART>::template weights<false>(P), cards, ncards, average, i, nevt,
-                     w_out ? RWGT_AT(w_in, i, nevt) : 0.0, w_out, me_out);
+    all_cards(Process<NPART>::template weights<false>(P), PairCards<NPART>{cards, ncards, average}, ncards, i, nevt,
+              w_out ? RWGT_AT(w_in, i, nevt) : 0.0, w_out, me_out);
   }
 }
 
-// rows null: all events.  A compute unit's LDS holds 14 (five particles) or 18
-// of event_kernel's waves; with 12 per unit the tiles are dealt evenly.
-template <int NPART, bool PRODUCT = false>
-inline hipError_t launch(const double* mom, int64_t nevt, const CardPair* cards, int ncards, double average,
-                         const double* w_in, double* w_out, double* me_out, const int32_t* rows,
-                         const unsigned int* nrows, hipStream_t s) {
+template <int NPART>
+inline size_t table(const CardPair* cards, int n, double average, void* out) {
+  return card_table<Couplings>(cards, n, out, [=](const Card<double>& c) { return couplings<NPART>(c, average); });
+}
+
+// A compute unit's LDS holds 14 (five particles) or 18 of event_kernel's
+// waves; with 12 per unit the tiles are dealt evenly.
+template <int NPART>
+inline hipError_t launch(const Fp64Call& a, double average, hipStream_t s) {
+  constexpr int64_t kWaves = 12 * 256;
+  static_assert(kWaves <= kNonfiniteBlocks, "every workgroup has a count");
+  const int64_t tiles = (a.nevt + 63) / 64, rounds = (tiles + kWaves - 1) / kWaves;
+  const int64_t blocks = (tiles + rounds - 1) / rounds;
+  if (a.counts) *a.counts = a.nonfinite ? int(blocks) : 0;
+  auto of = [=](const Card<double>& c) { return couplings<NPART>(c, average); };
+  return with_cards<Couplings>(a, of, [&](const auto& cards) {
+    typedef std::remove_cv_t<std::remove_reference_t<decltype(cards)>> Cards;
+    const auto kernel = a.scan ? event_kernel<NPART, true, Cards> : event_kernel<NPART, false, Cards>;
+    hipLaunchKernelGGL(kernel, dim3(unsigned(blocks)), dim3(64), 0, s, a.mom, a.nevt, cards, a.ncards, a.w_in, a.w_out,
+                       a.me_out, a.nonfinite);
+    return hipGetLastError();
+  });
+}
+
+template <int NPART>
+inline hipError_t launch_rows(const double* mom, int64_t nevt, const CardPair* cards, int ncards, double average,
+                              const double* w_in, double* w_out, double* me_out, const int32_t* rows,
+                              const unsigned int* nrows, hipStream_t s) {
   const int64_t tiles = (nevt + 63) / 64;
-  if (rows) {
-    hipLaunchKernelGGL(listed_kernel<NPART>, dim3(unsigned(tiles < 1024 ? tiles : 1024)), dim3(64), 0, s, mom, nevt,
-                       cards, ncards, average, w_in, w_out, me_out, rows, nrows);
-  } else {
-    constexpr int64_t kWaves = 12 * 256;
-    const int64_t rounds = (tiles + kWaves - 1) / kWaves, blocks = (tiles + rounds - 1) / rounds;
-    hipLaunchKernelGGL((event_kernel<NPART, PRODUCT>), dim3(unsigned(blocks)), dim3(64), 0, s, mom, nevt, cards,
-                       ncards, average, w_in, w_out, me_out);
-  }
+  hipLaunchKernelGGL(listed_kernel<NPART>, dim3(unsigned(tiles < 1024 ? tiles : 1024)), dim3(64), 0, s, mom, nevt,
+                     cards, ncards, average, w_in, w_out, me_out, rows, nrows);
   return hipGetLastError();
 }
 

@@ -24,20 +24,39 @@ constexpr int kMeBlock = 256;
 
 hipError_t launch_ingest(int npart, const double* aos, double* soa, int64_t nevt, hipStream_t s);
 
-// cards[0..ncards): |M|^2 per card -> me_out[k][nevt] (if non-null); when
+// Cards that travel as arguments of a double-precision launch (card_source.h).
+constexpr int kArgCards = 32;
+
+// Double precision, every event of the caller's mom ([nevt][npart][4]) under
+// every card: |M|^2 -> me_out[k][nevt] (if non-null); when w_out is non-null,
+// card 0 is the original and w_out[k-1][i] = (w_in[i] * (1/|M|^2_0)) * |M|^2_k
+// for k >= 1.  scan (electroweak processes): the lepton pair's mass squared as
+// twice a product (electroweak.h).  nonfinite (of kNonfiniteBlocks entries, or
+// null): each workgroup's count of the non-finite values among w_out, or among
+// me_out where w_out is null; *counts is the number of workgroups that counted,
+// 0 where there are too many of them for that (nothing is counted then).
+struct Fp64Call {
+  const double* mom = nullptr;
+  int64_t nevt = 0;
+  const CardPair* cards = nullptr;     // host
+  int ncards = 0;
+  const void* table = nullptr;         // device: fp64_table, where ncards > kArgCards
+  const double* w_in = nullptr;
+  double *w_out = nullptr, *me_out = nullptr;
+  bool scan = false;
+  unsigned long long* nonfinite = nullptr;
+  int* counts = nullptr;
+};
+hipError_t launch_fp64(int proc, const Fp64Call& a, hipStream_t s);
+// The table of cards[0 .. n), at most sizeof(CardPair) bytes each; its size.
+size_t fp64_table(int proc, const CardPair* cards, int n, void* out);
+
+// Mixed precision: cards[0..ncards): |M|^2 per card -> me_out[k][nevt] (if non-null); when
 // w_out is non-null, card 0 is the original card and
 // w_out[k-1][i] = (w_in[i] * (1/|M|^2_0)) * |M|^2_k for k >= 1.
-// mom: the caller's [nevt][npart][4] where me_reads_aos, else [npart * 4][nevt].
-bool me_reads_aos(int proc, int precision);
-hipError_t launch_me(int proc, int precision, const double* mom, int64_t nevt, const CardPair* cards, int ncards,
+// soa: [npart * 4][nevt].
+hipError_t launch_me(int proc, int precision, const double* soa, int64_t nevt, const CardPair* cards, int ncards,
                      const double* w_in, double* w_out, double* me_out, hipStream_t s);
-
-// The electroweak processes in double precision for a scan of cards: w_out as
-// launch_me, the lepton pair's mass squared as twice a product (electroweak.h).
-hipError_t launch_scan_ee_mumu(const double* mom, int64_t nevt, const CardPair* cards, int ncards, const double* w_in,
-                               double* w_out, hipStream_t s);
-hipError_t launch_scan_uu_eeg(const double* mom, int64_t nevt, const CardPair* cards, int ncards, const double* w_in,
-                              double* w_out, hipStream_t s);
 
 // Default threshold of the mixed path's cancellation guard: measured on 4e6
 // g g -> t t~ g g events (FP16 colour sum), it re-evaluates 0.10 % of them and
@@ -89,7 +108,7 @@ hipError_t launch_alphas(double* w_out, int64_t nevt, int nsets, const double* a
 // Non-finite entries (NaN, +-inf) of x[0..n): block b of the launch writes
 // its count to part[b]; the launch uses nonfinite_blocks(n) blocks (at most
 // kNonfiniteBlocks), so part needs that many entries.
-constexpr int kNonfiniteBlocks = 1024;
+constexpr int kNonfiniteBlocks = 4096;
 int nonfinite_blocks(int64_t n);
 hipError_t launch_nonfinite(const double* x, int64_t n, unsigned long long* part, hipStream_t s);
 
@@ -97,7 +116,9 @@ void process_constants(int proc, int* npart, int* ngood, int* ncol, int* ndiag);
 double process_flops(int proc, bool executed);
 
 #define RWGT_DECLARE_PROCESS(NAME)                                                                        \
-  hipError_t launch_me_##NAME(int precision, const double* mom, int64_t nevt, const CardPair* cards,     \
+  hipError_t launch_fp64_##NAME(const Fp64Call& a, hipStream_t s);                                       \
+  size_t fp64_table_##NAME(const CardPair* cards, int n, void* out);                                     \
+  hipError_t launch_me_##NAME(int precision, const double* soa, int64_t nevt, const CardPair* cards,     \
                               int ncards, const double* w_in, double* w_out, double* me_out, hipStream_t s); \
   hipError_t launch_me_guarded_##NAME(int precision, const double* soa, const double* mom, int64_t nevt,  \
                                       const CardPair* cards, int ncards, const double* w_in,             \
@@ -110,13 +131,16 @@ RWGT_DECLARE_PROCESS(gg_ttgg)
 RWGT_DECLARE_PROCESS(gg_tttt)
 #undef RWGT_DECLARE_PROCESS
 
-// Double precision by the colour-ordered recursions (ordered.h, ordered_pairs.h);
-// rows: only the events rows[0 .. *nrows) (device), null: all.
-hipError_t launch_ordered_gg_ttgg(const double* mom, int64_t nevt, const CardPair* cards, int ncards,
-                                  const double* w_in, double* w_out, double* me_out, const int32_t* rows,
-                                  const unsigned int* nrows, hipStream_t s);
-hipError_t launch_ordered_gg_tttt(const double* mom, int64_t nevt, const CardPair* cards, int ncards,
-                                  const double* w_in, double* w_out, double* me_out, const int32_t* rows,
-                                  const unsigned int* nrows, hipStream_t s);
+size_t qcd_table(const CardPair* cards, int n, void* out);
+// The QCD processes' double-precision kernels (ordered_kernel.h): all events,
+// or the events rows[0 .. *nrows) (device) under the mixed path's cards.
+hipError_t launch_ordered_gg_ttgg(const Fp64Call& a, hipStream_t s);
+hipError_t launch_ordered_gg_tttt(const Fp64Call& a, hipStream_t s);
+hipError_t launch_ordered_rows_gg_ttgg(const double* mom, int64_t nevt, const CardPair* cards, int ncards,
+                                       const double* w_in, double* w_out, double* me_out, const int32_t* rows,
+                                       const unsigned int* nrows, hipStream_t s);
+hipError_t launch_ordered_rows_gg_tttt(const double* mom, int64_t nevt, const CardPair* cards, int ncards,
+                                       const double* w_in, double* w_out, double* me_out, const int32_t* rows,
+                                       const unsigned int* nrows, hipStream_t s);
 
 }  // namespace rwgt

@@ -1,13 +1,14 @@
 // Device kernels of the reweighting path (gfx950, wave64):
 //   ingest_kernel  AoS [nevt][npart][4] -> SoA [npart*4][nevt] through LDS
-//   launch_me      dispatch to the per-process matrix-element kernels
-//                  (me_kernel.h, proc_<name>.hip)
+//   launch_fp64,   dispatch to the per-process matrix-element kernels
+//   launch_me      (electroweak_kernel.h, ordered_kernel.h; me_kernel.h)
 //   xsec_*         reweighted cross sections and errors per card
 //   factored       coupling-factored reweighting of many cards
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
 
+#include "card_source.h"
 #include "check.h"
 #include "kernels.h"
 
@@ -303,16 +304,38 @@ hipError_t launch_ingest(int npart, const double* aos, double* soa, int64_t nevt
   return hipGetLastError();
 }
 
-// The double-precision kernels read the caller's layout.
-bool me_reads_aos(int, int precision) { return precision == kPrecFP64; }
+hipError_t launch_fp64(int proc, const Fp64Call& a, hipStream_t s) {
+  if (a.nevt < 1 || a.ncards < 1 || !a.cards || (a.ncards > kArgCards && !a.table) || !a.mom ||
+      (a.w_out ? !a.w_in : !a.me_out))
+    return hipErrorInvalidValue;
+  switch (proc) {
+    case kProcEeMumu: return launch_fp64_ee_mumu(a, s);
+    case kProcUuEeg: return launch_fp64_uu_eeg(a, s);
+    case kProcGgTtgg: return launch_fp64_gg_ttgg(a, s);
+    case kProcGgTttt: return launch_fp64_gg_tttt(a, s);
+  }
+  return hipErrorInvalidValue;
+}
 
-hipError_t launch_me(int proc, int precision, const double* mom, int64_t nevt, const CardPair* cards, int ncards,
+size_t qcd_table(const CardPair* cards, int n, void* out) { return card_table<QcdCard>(cards, n, out, qcd_card); }
+
+size_t fp64_table(int proc, const CardPair* cards, int n, void* out) {
+  switch (proc) {
+    case kProcEeMumu: return fp64_table_ee_mumu(cards, n, out);
+    case kProcUuEeg: return fp64_table_uu_eeg(cards, n, out);
+    case kProcGgTtgg: return fp64_table_gg_ttgg(cards, n, out);
+    case kProcGgTttt: return fp64_table_gg_tttt(cards, n, out);
+  }
+  return 0;
+}
+
+hipError_t launch_me(int proc, int precision, const double* soa, int64_t nevt, const CardPair* cards, int ncards,
                      const double* w_in, double* w_out, double* me_out, hipStream_t s) {
   switch (proc) {
-    case kProcEeMumu: return launch_me_ee_mumu(precision, mom, nevt, cards, ncards, w_in, w_out, me_out, s);
-    case kProcUuEeg: return launch_me_uu_eeg(precision, mom, nevt, cards, ncards, w_in, w_out, me_out, s);
-    case kProcGgTtgg: return launch_me_gg_ttgg(precision, mom, nevt, cards, ncards, w_in, w_out, me_out, s);
-    case kProcGgTttt: return launch_me_gg_tttt(precision, mom, nevt, cards, ncards, w_in, w_out, me_out, s);
+    case kProcEeMumu: return launch_me_ee_mumu(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, s);
+    case kProcUuEeg: return launch_me_uu_eeg(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, s);
+    case kProcGgTtgg: return launch_me_gg_ttgg(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, s);
+    case kProcGgTttt: return launch_me_gg_tttt(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, s);
   }
   return hipErrorInvalidValue;
 }

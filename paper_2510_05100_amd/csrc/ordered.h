@@ -284,8 +284,8 @@ RWGT_HD void half_terms(M& m, int t, int a, int b, int c, int d, int row0, int c
 // columns are the caller's: COLOUR(f) is J^dagger C J of the 24 flows.
 //   pt, ptb   momenta of the outgoing quark and antiquark (E px py pz)
 // Returns |M_h|^2 summed over colours, without g^2 of the last vertices.
-template <class R, class M, class Sync, class Colour>
-RWGT_HD R lane_me2(M& m, int t, const R* pt, const R* ptb, const Card<R, R>& cd, Sync sync, Colour colour) {
+template <class R, class M, class Cd, class Sync, class Colour>
+RWGT_HD R lane_me2(M& m, int t, const R* pt, const R* ptb, const Cd& cd, Sync sync, Colour colour) {
   const LaneHel h = lane_hel(t);
   const Quarks<R> q = {lc_momentum(pt, R(1)), lc_momentum(ptb, R(1)), cd.mt};
   auto clamp = [&](int n) { const int x = opq_index(t); return x < n ? x : n - 1; };   // idle lanes repeat the last task

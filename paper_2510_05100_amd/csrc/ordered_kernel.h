@@ -5,7 +5,9 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
+#include "card_source.h"
 #include "check.h"
 #include "helas.h"
 #include "kernels.h"
@@ -81,9 +83,9 @@ struct QuarkLine {                               // g g -> Q Q~ g g
     load_momentum(mom, nevt, 6, g < 2 ? g : g + 2, i, p);
     m.set_mom(g, lc_momentum(p, g < 2 ? 1.0 : -1.0));
   }
-  template <class Colour>
+  template <class Cd, class Colour>
   static __device__ __forceinline__ double lane(Memory& m, int t, const double* mom, int64_t nevt, int64_t i,
-                                                const Card<double>& cd, Colour colour) {
+                                                const Cd& cd, Colour colour) {
     double pt[4], ptb[4];
     load_momentum(mom, nevt, 6, 2, i, pt);
     load_momentum(mom, nevt, 6, 3, i, ptb);
@@ -98,11 +100,11 @@ struct QuarkPairs {                              // g g -> Q Q~ Q Q~
     load_momentum(mom, nevt, 6, a, i, p);
     m.set_mom(a, lc_momentum(p, 1.0));
   }
-  template <class Colour>
+  template <class Cd, class Colour>
   static __device__ __forceinline__ double lane(Memory& m, int t, const double* mom, int64_t nevt, int64_t i,
-                                                const Card<double>& cd, Colour colour) {
+                                                const Cd& cd, Colour colour) {
     auto load = [&](int a, double (&p)[4]) { load_momentum(mom, nevt, 6, a, i, p); };
-    return pairs::lane_me2(m, t, load, cd, [] { wave_sync(); }, colour);
+    return pairs::lane_me2<double>(m, t, load, cd, [] { wave_sync(); }, colour);
   }
 };
 
@@ -114,26 +116,28 @@ struct QuarkPairs {                              // g g -> Q Q~ Q Q~
 // A wave evaluates a card of its two events in 6300 vector instructions, where
 // evaluating every diagram for every helicity takes about 5 times that
 // (g g -> t t~ g g; g g -> t t~ t t~ 4 times).  Two waves per SIMD (LDS 17 KB
-// per wave, 256 registers, 25 spilled; 164, none) hide the LDS latency; the
+// per wave, 256 registers, 28 spilled; 166, none) hide the LDS latency; the
 // fences (load_fence, settle) hold the compiler to the order of the source,
 // without them it loads everything first and spills 1000 registers.  1e6
 // events, one new card: 12.5 - 14.4 ms (from card to card; 75 ms diagram by
 // diagram, one lane per event and two waves splitting its helicities), 777
-// events: 0.043 (2.4) ms; g g -> t t~ t t~, 250001 events: 2.48 (9.32) ms.  A
+// events: 0.035 (2.4) ms; g g -> t t~ t t~, 250001 events: 2.48 (9.32) ms.  A
 // first form for g g -> t t~ g g with two waves per 64
 // events and one lane per event shared the gluon currents only and needed 512
 // registers with 310 spilled, waiting in half of its cycles: 29.7 ms.
-template <class PROC, class REC, bool LISTED>
+template <class PROC, class REC, bool LISTED, class CARDS>
 __global__ __launch_bounds__(64, 2) void ordered_kernel(const double* __restrict__ mom, int64_t nevt,
-                                                        const CardPair* __restrict__ cards, int ncards,
+                                                        const CARDS cards, int ncards,
                                                         const double* __restrict__ w_in, double* __restrict__ w_out,
                                                         double* __restrict__ me_out, const int32_t* __restrict__ rows,
-                                                        const unsigned int* __restrict__ nrows) {
+                                                        const unsigned int* __restrict__ nrows,
+                                                        unsigned long long* __restrict__ nonfinite) {
   __shared__ typename REC::Memory::Event mem[2];
   const int t = int(threadIdx.x) & (kLanes - 1), half = int(threadIdx.x) / kLanes;
   typename REC::Memory m{&mem[half]};
   const int64_t n = LISTED ? int64_t(*nrows) : nevt;
   int64_t first = int64_t(blockIdx.x) * 2;
+  int bad = 0;                                   // non-finite outputs of this half's events
   if (LISTED && first >= n) return;
   do {
     const bool valid = first + half < n;
@@ -144,7 +148,7 @@ __global__ __launch_bounds__(64, 2) void ordered_kernel(const double* __restrict
     double norm = 0.0;
 #pragma unroll 1
     for (int k = 0; k < ncards; ++k) {
-      const Card<double>& cd = RWGT_AT(cards, k, ncards).d;
+      const auto& cd = cards(k);                 // read where it is used: held, it would cost registers
       wave_sync();
       double me = REC::lane(m, opq_index(t), mom, nevt, i, cd, [](const cx<double>(&f)[PROC::NCOL]) {
         return PROC::template colour_sum<double>(f);
@@ -158,24 +162,55 @@ __global__ __launch_bounds__(64, 2) void ordered_kernel(const double* __restrict
         if (k == 0) {
           norm = (me == 0.0 ? 0.0 : 1.0 / me) * RWGT_AT(w_in, i, nevt);
         } else {
-          RWGT_AT(w_out, int64_t(k - 1) * nevt + i, int64_t(ncards - 1) * nevt) = norm * me;
+          const double w = norm * me;
+          RWGT_AT(w_out, int64_t(k - 1) * nevt + i, int64_t(ncards - 1) * nevt) = w;
+          if (!LISTED) bad += isfinite(w) ? 0 : 1;
         }
+      } else if (!LISTED) {
+        bad += isfinite(me) ? 0 : 1;
       }
     }
     first += int64_t(gridDim.x) * 2;
   } while (LISTED && first < n);
+  if (!LISTED && nonfinite) {
+    bad += __shfl_xor(bad, kLanes);
+    if (threadIdx.x == 0) RWGT_AT(nonfinite, blockIdx.x, gridDim.x) = static_cast<unsigned long long>(bad);
+  }
 }
+
+// The workgroups count their non-finite outputs as long as there are few
+// enough of them for the caller to add up (8192 events; beyond, the separate
+// pass is under 2 % of the call).
+template <class PROC, class REC>
+inline hipError_t launch(const Fp64Call& a, hipStream_t s) {
+  const int64_t blocks = (a.nevt + 1) / 2;
+  const bool count = a.nonfinite && blocks <= kNonfiniteBlocks;
+  if (a.counts) *a.counts = count ? int(blocks) : 0;
+  return with_cards<QcdCard>(a, qcd_card, [&](const auto& cards) {
+    typedef std::remove_cv_t<std::remove_reference_t<decltype(cards)>> Cards;
+    hipLaunchKernelGGL((ordered_kernel<PROC, REC, false, Cards>), dim3(unsigned(blocks)), dim3(64), 0, s, a.mom,
+                       a.nevt, cards, a.ncards, a.w_in, a.w_out, a.me_out, static_cast<const int32_t*>(nullptr),
+                       static_cast<const unsigned int*>(nullptr), count ? a.nonfinite : nullptr);
+    return hipGetLastError();
+  });
+}
+
+struct PairCards {                               // the mixed path's cards
+  const CardPair* p;
+  int n;
+  __device__ __forceinline__ const Card<double>& operator()(int k) const { return RWGT_AT(p, k, n).d; }
+};
 
 // rows: at most nevt of them, counted on the device; 4096 workgroups keep
 // every SIMD at its two waves twice over.
 template <class PROC, class REC>
-inline hipError_t launch_ordered(const double* mom, int64_t nevt, const CardPair* cards, int ncards,
-                                 const double* w_in, double* w_out, double* me_out, const int32_t* rows,
-                                 const unsigned int* nrows, hipStream_t s) {
-  const int64_t pairs = (nevt + 1) / 2, blocks = rows && pairs > 4096 ? 4096 : pairs;
-  const auto kernel = rows ? ordered_kernel<PROC, REC, true> : ordered_kernel<PROC, REC, false>;
-  hipLaunchKernelGGL(kernel, dim3(unsigned(blocks)), dim3(64), 0, s, mom, nevt, cards, ncards, w_in, w_out, me_out,
-                     rows, nrows);
+inline hipError_t launch_rows(const double* mom, int64_t nevt, const CardPair* cards, int ncards, const double* w_in,
+                              double* w_out, double* me_out, const int32_t* rows, const unsigned int* nrows,
+                              hipStream_t s) {
+  const int64_t pairs = (nevt + 1) / 2;
+  hipLaunchKernelGGL((ordered_kernel<PROC, REC, true, PairCards>), dim3(unsigned(pairs < 4096 ? pairs : 4096)),
+                     dim3(64), 0, s, mom, nevt, PairCards{cards, ncards}, ncards, w_in, w_out, me_out, rows, nrows,
+                     static_cast<unsigned long long*>(nullptr));
   return hipGetLastError();
 }
 

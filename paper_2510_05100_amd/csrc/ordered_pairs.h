@@ -284,8 +284,8 @@ template <class R, class M> RWGT_HD void shared_terms(M& m, int t, int b, cx<R> 
 
 // One lane's part of an event: |M_h|^2 summed over colours, without g^2 of the
 // last vertices.  momentum(a, p) loads particle a's momentum (E px py pz).
-template <class R, class M, class Load, class Sync, class Colour>
-RWGT_HD R lane_me2(M& m, int t, Load momentum, const Card<R, R>& cd, Sync sync, Colour colour) {
+template <class R, class M, class Load, class Cd, class Sync, class Colour>
+RWGT_HD R lane_me2(M& m, int t, Load momentum, const Cd& cd, Sync sync, Colour colour) {
   auto clamp = [&](int n) { const int x = opq_index(t); return x < n ? x : n - 1; };   // idle lanes repeat the last task
   {
     const int n = clamp(8);

@@ -8,16 +8,16 @@ namespace rwgt {
 
 RWGT_PROCESS_TRAITS(ee_mumu)
 
-hipError_t launch_me_ee_mumu(int precision, const double* mom, int64_t nevt, const CardPair* cards, int ncards,
-                            const double* w_in, double* w_out, double* me_out, hipStream_t s) {
-  if (precision == kPrecFP64)
-    return ew::launch<4>(mom, nevt, cards, ncards, gen_ee_mumu::AVERAGE, w_in, w_out, me_out, nullptr, nullptr, s);
-  return launch_me_prec<Proc_ee_mumu>(precision, mom, nevt, cards, ncards, w_in, w_out, me_out, s);
+hipError_t launch_fp64_ee_mumu(const Fp64Call& a, hipStream_t s) {
+  return ew::launch<4>(a, gen_ee_mumu::AVERAGE, s);
+}
+size_t fp64_table_ee_mumu(const CardPair* cards, int n, void* out) {
+  return ew::table<4>(cards, n, gen_ee_mumu::AVERAGE, out);
 }
 
-hipError_t launch_scan_ee_mumu(const double* mom, int64_t nevt, const CardPair* cards, int ncards, const double* w_in,
-                          double* w_out, hipStream_t s) {
-  return ew::launch<4, true>(mom, nevt, cards, ncards, gen_ee_mumu::AVERAGE, w_in, w_out, nullptr, nullptr, nullptr, s);
+hipError_t launch_me_ee_mumu(int precision, const double* soa, int64_t nevt, const CardPair* cards, int ncards,
+                         const double* w_in, double* w_out, double* me_out, hipStream_t s) {
+  return launch_me_prec<Proc_ee_mumu>(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, s);
 }
 
 hipError_t launch_me_guarded_ee_mumu(int precision, const double* soa, const double* mom, int64_t nevt,
@@ -25,7 +25,8 @@ hipError_t launch_me_guarded_ee_mumu(int precision, const double* soa, const dou
                                     const GuardArgs& g, hipStream_t s) {
   const hipError_t e = launch_me_flag_t<Proc_ee_mumu>(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, g, s);
   if (e != hipSuccess || !reevaluates(g)) return e;
-  return ew::launch<4>(mom, nevt, cards, ncards, gen_ee_mumu::AVERAGE, w_in, w_out, me_out, g.flagged, g.nflagged, s);
+  return ew::launch_rows<4>(mom, nevt, cards, ncards, gen_ee_mumu::AVERAGE, w_in, w_out, me_out, g.flagged, g.nflagged,
+                            s);
 }
 
 void constants_ee_mumu(int* npart, int* ngood, int* ncol, int* ndiag) {

@@ -7,11 +7,12 @@ namespace rwgt {
 
 RWGT_PROCESS_TRAITS(gg_tttt)
 
-hipError_t launch_me_gg_tttt(int precision, const double* mom, int64_t nevt, const CardPair* cards, int ncards,
-                            const double* w_in, double* w_out, double* me_out, hipStream_t s) {
-  if (precision == kPrecFP64)
-    return launch_ordered_gg_tttt(mom, nevt, cards, ncards, w_in, w_out, me_out, nullptr, nullptr, s);
-  return launch_me_prec<Proc_gg_tttt>(precision, mom, nevt, cards, ncards, w_in, w_out, me_out, s);
+hipError_t launch_fp64_gg_tttt(const Fp64Call& a, hipStream_t s) { return launch_ordered_gg_tttt(a, s); }
+size_t fp64_table_gg_tttt(const CardPair* cards, int n, void* out) { return qcd_table(cards, n, out); }
+
+hipError_t launch_me_gg_tttt(int precision, const double* soa, int64_t nevt, const CardPair* cards, int ncards,
+                         const double* w_in, double* w_out, double* me_out, hipStream_t s) {
+  return launch_me_prec<Proc_gg_tttt>(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, s);
 }
 
 hipError_t launch_me_guarded_gg_tttt(int precision, const double* soa, const double* mom, int64_t nevt,
@@ -19,7 +20,7 @@ hipError_t launch_me_guarded_gg_tttt(int precision, const double* soa, const dou
                                     const GuardArgs& g, hipStream_t s) {
   const hipError_t e = launch_me_flag_t<Proc_gg_tttt>(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, g, s);
   if (e != hipSuccess || !reevaluates(g)) return e;
-  return launch_ordered_gg_tttt(mom, nevt, cards, ncards, w_in, w_out, me_out, g.flagged, g.nflagged, s);
+  return launch_ordered_rows_gg_tttt(mom, nevt, cards, ncards, w_in, w_out, me_out, g.flagged, g.nflagged, s);
 }
 
 void constants_gg_tttt(int* npart, int* ngood, int* ncol, int* ndiag) {

@@ -8,16 +8,16 @@ namespace rwgt {
 
 RWGT_PROCESS_TRAITS(uu_eeg)
 
-hipError_t launch_me_uu_eeg(int precision, const double* mom, int64_t nevt, const CardPair* cards, int ncards,
-                            const double* w_in, double* w_out, double* me_out, hipStream_t s) {
-  if (precision == kPrecFP64)
-    return ew::launch<5>(mom, nevt, cards, ncards, gen_uu_eeg::AVERAGE, w_in, w_out, me_out, nullptr, nullptr, s);
-  return launch_me_prec<Proc_uu_eeg>(precision, mom, nevt, cards, ncards, w_in, w_out, me_out, s);
+hipError_t launch_fp64_uu_eeg(const Fp64Call& a, hipStream_t s) {
+  return ew::launch<5>(a, gen_uu_eeg::AVERAGE, s);
+}
+size_t fp64_table_uu_eeg(const CardPair* cards, int n, void* out) {
+  return ew::table<5>(cards, n, gen_uu_eeg::AVERAGE, out);
 }
 
-hipError_t launch_scan_uu_eeg(const double* mom, int64_t nevt, const CardPair* cards, int ncards, const double* w_in,
-                          double* w_out, hipStream_t s) {
-  return ew::launch<5, true>(mom, nevt, cards, ncards, gen_uu_eeg::AVERAGE, w_in, w_out, nullptr, nullptr, nullptr, s);
+hipError_t launch_me_uu_eeg(int precision, const double* soa, int64_t nevt, const CardPair* cards, int ncards,
+                         const double* w_in, double* w_out, double* me_out, hipStream_t s) {
+  return launch_me_prec<Proc_uu_eeg>(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, s);
 }
 
 hipError_t launch_me_guarded_uu_eeg(int precision, const double* soa, const double* mom, int64_t nevt,
@@ -25,7 +25,8 @@ hipError_t launch_me_guarded_uu_eeg(int precision, const double* soa, const doub
                                     const GuardArgs& g, hipStream_t s) {
   const hipError_t e = launch_me_flag_t<Proc_uu_eeg>(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, g, s);
   if (e != hipSuccess || !reevaluates(g)) return e;
-  return ew::launch<5>(mom, nevt, cards, ncards, gen_uu_eeg::AVERAGE, w_in, w_out, me_out, g.flagged, g.nflagged, s);
+  return ew::launch_rows<5>(mom, nevt, cards, ncards, gen_uu_eeg::AVERAGE, w_in, w_out, me_out, g.flagged, g.nflagged,
+                            s);
 }
 
 void constants_uu_eeg(int* npart, int* ngood, int* ncol, int* ndiag) {

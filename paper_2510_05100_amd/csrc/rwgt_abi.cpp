@@ -235,7 +235,7 @@ struct rwgt_ctx {
 namespace {
 
 int ensure_buffers(rwgt_ctx* c, int64_t nevt, int ncards) {
-  if (!rwgt::me_reads_aos(c->def->id, c->precision) && nevt > c->soa_events) {
+  if (c->precision != RWGT_FP64 && nevt > c->soa_events) {
     if (c->soa) {
       hipStreamSynchronize(c->stream);
       hipFree(c->soa);
@@ -298,9 +298,57 @@ int ensure_guard(rwgt_ctx* c, int64_t nevt) {
   return RWGT_OK;
 }
 
+// The pinned card buffer, once the previous upload from it is done.
+int cards_ready(rwgt_ctx* c) {
+  if (!c->upload_pending) return RWGT_OK;
+  const hipError_t e = hipEventSynchronize(c->upload_done);
+  if (e != hipSuccess) return c->hip_fail(e, "hipEventSynchronize");
+  c->upload_pending = false;
+  return RWGT_OK;
+}
+// bytes of hcards to dcards
+int upload_cards(rwgt_ctx* c, size_t bytes) {
+  hipError_t e = hipMemcpyAsync(c->dcards, c->hcards, bytes, hipMemcpyHostToDevice, c->stream);
+  if (e != hipSuccess) return c->hip_fail(e, "hipMemcpyAsync(cards)");
+  e = hipEventRecord(c->upload_done, c->stream);
+  if (e != hipSuccess) return c->hip_fail(e, "hipEventRecord");
+  c->upload_pending = true;
+  return RWGT_OK;
+}
+
+int ensure_nonfinite(rwgt_ctx* c) {
+  if (c->nf_part) return RWGT_OK;
+  const hipError_t e = hipMalloc(&c->nf_part, rwgt::kNonfiniteBlocks * sizeof(unsigned long long));
+  return e == hipSuccess ? RWGT_OK : c->hip_fail(e, "hipMalloc(non-finite counts)");
+}
+
+// The double-precision kernel of the context's process: cards as launch
+// arguments, or where there are more than those carry, uploaded.  Queues the
+// upload ahead of profiling event 0.
+int run_fp64(rwgt_ctx* c, rwgt::Fp64Call& a, const std::vector<CardPair>& cards) {
+  a.cards = cards.data();
+  a.ncards = int(cards.size());
+  if (a.ncards > rwgt::kArgCards) {
+    int rc = ensure_buffers(c, a.nevt, a.ncards);
+    if (rc == RWGT_OK) rc = cards_ready(c);
+    if (rc == RWGT_OK) rc = upload_cards(c, rwgt::fp64_table(c->def->id, a.cards, a.ncards, c->hcards));
+    if (rc != RWGT_OK) return rc;
+    a.table = c->dcards;
+  }
+  if (c->profiling) hipEventRecord(c->ev[0], c->stream);
+  if (c->profiling) hipEventRecord(c->ev[1], c->stream);
+  const hipError_t e = rwgt::launch_fp64(c->def->id, a, c->stream);
+  if (e != hipSuccess) return c->hip_fail(e, "matrix-element kernel");
+  if (c->profiling) hipEventRecord(c->ev[2], c->stream);
+  return RWGT_OK;
+}
+
+// count: the outputs are final, so a kernel that can counts the non-finite
+// ones on its way (nf_blocks > 0; see count_run).
 int run(rwgt_ctx* c, bool reweight, const double* momenta, int64_t nevt, const double* w_in,
         const double* param_sets, int32_t nsets, double* w_out, double* me_out, double* kappa_out = nullptr,
-        bool ew_scan = false) {
+        bool ew_scan = false, bool count = true) {
+  c->nf_blocks = 0;
   if (nevt < 0) return c->fail(RWGT_EINVAL, "nevt < 0");
   if (nsets < 1) return c->fail(RWGT_EINVAL, "nsets < 1");
   if (!param_sets) return c->fail(RWGT_EINVAL, "param_sets is NULL");
@@ -314,28 +362,34 @@ int run(rwgt_ctx* c, bool reweight, const double* momenta, int64_t nevt, const d
   if (!reweight && !me_out && !kappa_out) return c->fail(RWGT_EINVAL, "me2_out is NULL");
   hipError_t e = hipSetDevice(c->device);
   if (e != hipSuccess) return c->hip_fail(e, "hipSetDevice");
-  rc = ensure_buffers(c, nevt, int(cards.size()));
-  if (rc != RWGT_OK) return rc;
-  if (c->upload_pending) {
-    e = hipEventSynchronize(c->upload_done);
-    if (e != hipSuccess) return c->hip_fail(e, "hipEventSynchronize");
-    c->upload_pending = false;
-  }
-  std::memcpy(c->hcards, cards.data(), cards.size() * sizeof(CardPair));
-  e = hipMemcpyAsync(c->dcards, c->hcards, cards.size() * sizeof(CardPair), hipMemcpyHostToDevice, c->stream);
-  if (e != hipSuccess) return c->hip_fail(e, "hipMemcpyAsync(cards)");
-  e = hipEventRecord(c->upload_done, c->stream);
-  if (e != hipSuccess) return c->hip_fail(e, "hipEventRecord");
-  c->upload_pending = true;
-  if (c->profiling) hipEventRecord(c->ev[0], c->stream);
-  const bool aos = rwgt::me_reads_aos(c->def->id, c->precision);
-  if (!aos) {
-    e = rwgt::launch_ingest(c->def->npart, momenta, c->soa, nevt, c->stream);
-    if (e != hipSuccess) return c->hip_fail(e, "ingest kernel");
-  }
-  if (c->profiling) hipEventRecord(c->ev[1], c->stream);
   c->guard_ran = false;
-  if (c->precision != RWGT_FP64 && (kappa_out || c->guard_kmax > 0.0)) {
+  if (c->precision == RWGT_FP64) {
+    rwgt::Fp64Call a;
+    a.mom = momenta;
+    a.nevt = nevt;
+    a.w_in = w_in;
+    a.w_out = w_out;
+    a.me_out = me_out;
+    a.scan = ew_scan;
+    if (count) {
+      rc = ensure_nonfinite(c);
+      if (rc != RWGT_OK) return rc;
+      a.nonfinite = c->nf_part;
+      a.counts = &c->nf_blocks;
+    }
+    return run_fp64(c, a, cards);
+  }
+  rc = ensure_buffers(c, nevt, int(cards.size()));
+  if (rc == RWGT_OK) rc = cards_ready(c);
+  if (rc != RWGT_OK) return rc;
+  std::memcpy(c->hcards, cards.data(), cards.size() * sizeof(CardPair));
+  rc = upload_cards(c, cards.size() * sizeof(CardPair));
+  if (rc != RWGT_OK) return rc;
+  if (c->profiling) hipEventRecord(c->ev[0], c->stream);
+  e = rwgt::launch_ingest(c->def->npart, momenta, c->soa, nevt, c->stream);
+  if (e != hipSuccess) return c->hip_fail(e, "ingest kernel");
+  if (c->profiling) hipEventRecord(c->ev[1], c->stream);
+  if (kappa_out || c->guard_kmax > 0.0) {
     rwgt::GuardArgs g;
     if (kappa_out) {                             // kappa only: nothing flagged or re-evaluated
       g.kmax = -1.0;
@@ -350,12 +404,9 @@ int run(rwgt_ctx* c, bool reweight, const double* momenta, int64_t nevt, const d
     }
     e = rwgt::launch_me_guarded(c->def->id, c->precision, c->soa, momenta, nevt, c->dcards, int(cards.size()), w_in,
                                 w_out, me_out, g, c->stream);
-  } else if (ew_scan) {
-    e = (c->def->id == rwgt::kProcEeMumu ? rwgt::launch_scan_ee_mumu : rwgt::launch_scan_uu_eeg)(
-        momenta, nevt, c->dcards, int(cards.size()), w_in, w_out, c->stream);
   } else {
-    e = rwgt::launch_me(c->def->id, c->precision, aos ? momenta : c->soa, nevt, c->dcards, int(cards.size()), w_in,
-                        w_out, me_out, c->stream);
+    e = rwgt::launch_me(c->def->id, c->precision, c->soa, nevt, c->dcards, int(cards.size()), w_in, w_out, me_out,
+                        c->stream);
   }
   if (e != hipSuccess) return c->hip_fail(e, "matrix-element kernel");
   if (c->profiling) hipEventRecord(c->ev[2], c->stream);
@@ -367,15 +418,17 @@ int run(rwgt_ctx* c, bool reweight, const double* momenta, int64_t nevt, const d
 int count_nonfinite(rwgt_ctx* c, const double* out, int64_t n) {
   c->nf_blocks = 0;
   if (n <= 0) return RWGT_OK;
-  hipError_t e = hipSuccess;
-  if (!c->nf_part) {
-    e = hipMalloc(&c->nf_part, rwgt::kNonfiniteBlocks * sizeof(unsigned long long));
-    if (e != hipSuccess) return c->hip_fail(e, "hipMalloc(non-finite counts)");
-  }
-  e = rwgt::launch_nonfinite(out, n, c->nf_part, c->stream);
+  const int rc = ensure_nonfinite(c);
+  if (rc != RWGT_OK) return rc;
+  const hipError_t e = rwgt::launch_nonfinite(out, n, c->nf_part, c->stream);
   if (e != hipSuccess) return c->hip_fail(e, "non-finite count kernel");
   c->nf_blocks = rwgt::nonfinite_blocks(n);
   return RWGT_OK;
+}
+
+// The same after run(), whose kernel may have counted on its way.
+int count_run(rwgt_ctx* c, const double* out, int64_t n) {
+  return c->nf_blocks > 0 ? RWGT_OK : count_nonfinite(c, out, n);
 }
 
 // Where a caller array lives.  Memory of this context's device (device or
@@ -542,7 +595,7 @@ int rwgt_eval(rwgt_ctx* ctx, const double* momenta, int64_t nevt, const double* 
     Staged st{momenta, weights_in, weights_out};
     int rc = st.begin(ctx, nevt, int64_t(nsets) * nevt);
     if (rc == RWGT_OK) rc = run(ctx, true, st.mom, nevt, st.w_in, param_sets, nsets, st.out, nullptr);
-    if (rc == RWGT_OK) rc = count_nonfinite(ctx, st.out, int64_t(nsets) * nevt);
+    if (rc == RWGT_OK) rc = count_run(ctx, st.out, int64_t(nsets) * nevt);
     return rc == RWGT_OK ? st.finish(ctx) : rc;
   } catch (const std::exception& ex) {
     return ctx->fail(RWGT_ENOMEM, ex.what());
@@ -558,11 +611,13 @@ int rwgt_eval_alphas(rwgt_ctx* c, const double* momenta, int64_t nevt, const dou
   c->err.clear();
   c->nf_blocks = 0;
   if (nevt > 0 && !scales) return c->fail(RWGT_EINVAL, "scales is NULL");
-  int rc = run(c, true, momenta, nevt, w_in, param_sets, nsets, w_out, nullptr);
+  // the electroweak pair carries no alpha_s: its weights are final as they are
+  const bool final = c->def->id == rwgt::kProcEeMumu;
+  int rc = run(c, true, momenta, nevt, w_in, param_sets, nsets, w_out, nullptr, nullptr, false, final);
   if (rc != RWGT_OK || nevt == 0) return rc;
   const int id = c->def->id;
   const int p = id == rwgt::kProcEeMumu ? 0 : id == rwgt::kProcUuEeg ? 1 : 4;   // power of alpha_s in |M|^2
-  if (p == 0) return count_nonfinite(c, w_out, int64_t(nsets) * nevt);
+  if (p == 0) return count_run(c, w_out, int64_t(nsets) * nevt);
   const auto& layout = c->def->layout;
   int ja = -1;
   for (size_t j = 0; j < layout.size(); ++j)
@@ -606,7 +661,7 @@ int rwgt_eval_factored(rwgt_ctx* c, const double* momenta, int64_t nevt, const d
     if (c->precision == RWGT_FP64 && (c->def->id == rwgt::kProcEeMumu || c->def->id == rwgt::kProcUuEeg)) {
       // the double-precision electroweak kernel is factored itself: each event's weights once, then every card
       const int done = run(c, true, momenta, nevt, w_in, param_sets, nsets, w_out, nullptr, nullptr, true);
-      return done == RWGT_OK ? count_nonfinite(c, w_out, int64_t(nsets) * nevt) : done;
+      return done == RWGT_OK ? count_run(c, w_out, int64_t(nsets) * nevt) : done;
     }
     std::vector<CardPair> cards;
     int rc = build_cards(c, param_sets, nsets, true, cards);
@@ -655,7 +710,8 @@ int rwgt_eval_factored(rwgt_ctx* c, const double* momenta, int64_t nevt, const d
     const int nprobe = int(probes.size());
     hipError_t e = hipSetDevice(c->device);
     if (e != hipSuccess) return c->hip_fail(e, "hipSetDevice");
-    rc = ensure_buffers(c, nevt, nprobe);
+    const bool fp64 = c->precision == RWGT_FP64;
+    rc = fp64 ? RWGT_OK : ensure_buffers(c, nevt, nprobe);
     if (rc != RWGT_OK) return rc;
     if (int64_t(nprobe) * nevt > c->fac_probe_cap) {
       if (c->fac_probe) { (void)hipStreamSynchronize(c->stream); (void)hipFree(c->fac_probe); c->fac_probe = nullptr; }
@@ -671,26 +727,32 @@ int rwgt_eval_factored(rwgt_ctx* c, const double* momenta, int64_t nevt, const d
       if (e != hipSuccess) return c->hip_fail(e, "hipMalloc(factor cards)");
       c->fac_cards_cap = int(fc.size());
     }
-    if (c->upload_pending) {
-      e = hipEventSynchronize(c->upload_done);
-      if (e != hipSuccess) return c->hip_fail(e, "hipEventSynchronize");
-      c->upload_pending = false;
+    if (!fp64) {
+      rc = cards_ready(c);
+      if (rc != RWGT_OK) return rc;
+      std::memcpy(c->hcards, probes.data(), probes.size() * sizeof(CardPair));
+      rc = upload_cards(c, probes.size() * sizeof(CardPair));
+      if (rc != RWGT_OK) return rc;
     }
-    std::memcpy(c->hcards, probes.data(), probes.size() * sizeof(CardPair));
-    e = hipMemcpyAsync(c->dcards, c->hcards, probes.size() * sizeof(CardPair), hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess) e = hipEventRecord(c->upload_done, c->stream);
-    if (e != hipSuccess) return c->hip_fail(e, "probe card upload");
-    c->upload_pending = true;
     // the factor table comes from pageable memory: wait for that copy
     e = hipMemcpyAsync(c->fac_cards, fc.data(), fc.size() * sizeof(rwgt::FactorCard), hipMemcpyHostToDevice,
                        c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return c->hip_fail(e, "factor card upload");
-    const bool aos = rwgt::me_reads_aos(id, c->precision);
-    if (!aos) e = rwgt::launch_ingest(c->def->npart, momenta, c->soa, nevt, c->stream);
-    if (e == hipSuccess)
-      e = rwgt::launch_me(id, c->precision, aos ? momenta : c->soa, nevt, c->dcards, nprobe, nullptr, nullptr,
-                          c->fac_probe, c->stream);
+    if (fp64) {
+      rwgt::Fp64Call a;
+      a.mom = momenta;
+      a.nevt = nevt;
+      a.cards = probes.data();
+      a.ncards = nprobe;
+      a.me_out = c->fac_probe;
+      e = rwgt::launch_fp64(id, a, c->stream);
+    } else {
+      e = rwgt::launch_ingest(c->def->npart, momenta, c->soa, nevt, c->stream);
+      if (e == hipSuccess)
+        e = rwgt::launch_me(id, c->precision, c->soa, nevt, c->dcards, nprobe, nullptr, nullptr, c->fac_probe,
+                            c->stream);
+    }
     if (e == hipSuccess)
       e = rwgt::launch_factored(ew, c->soa, c->def->npart, nevt, ia, ib, c->fac_probe, o.mz, o.wz, c->fac_cards,
                                 int(fc.size()), w_in, w_out, c->stream);
@@ -711,7 +773,7 @@ int rwgt_me2(rwgt_ctx* ctx, const double* momenta, int64_t nevt, const double* p
     Staged st{momenta, nullptr, me2_out};
     int rc = st.begin(ctx, nevt, int64_t(nsets) * nevt);
     if (rc == RWGT_OK) rc = run(ctx, false, st.mom, nevt, nullptr, param_sets, nsets, nullptr, st.out);
-    if (rc == RWGT_OK) rc = count_nonfinite(ctx, st.out, int64_t(nsets) * nevt);
+    if (rc == RWGT_OK) rc = count_run(ctx, st.out, int64_t(nsets) * nevt);
     return rc == RWGT_OK ? st.finish(ctx) : rc;
   } catch (const std::exception& ex) {
     return ctx->fail(RWGT_ENOMEM, ex.what());

@@ -72,7 +72,7 @@ int main() {
         const double* p = &P[size_t(e * 24)];
 #ifdef PAIRS
         auto load = [&](int a, double (&q)[4]) { for (int m = 0; m < 4; ++m) q[m] = p[4 * a + m]; };
-        part[size_t(e * 32 + t)] = pairs::lane_me2(mem[size_t(e)], t, load, cd, sync, colour);
+        part[size_t(e * 32 + t)] = pairs::lane_me2<double>(mem[size_t(e)], t, load, cd, sync, colour);
 #else
         part[size_t(e * 32 + t)] = lane_me2(mem[size_t(e)], t, p + 8, p + 12, cd, sync, colour);
 #endif
