@@ -113,10 +113,11 @@ hipError_t mlp_infer(int width, const InferArgs& a, hipStream_t s);
 
 // Fused training step of the networks the fused inference kernel runs (two
 // heads).  mlp_train_grads: every row tile's inputs, forward and backward
-// pass, and per workgroup the sums over its rows of every gradient (and of
-// the loss) into its slot of part; mlp_train_update: those sums added in
-// workgroup order into the gradient buffers, then (adam) the Adam step and
-// every copy of each new parameter.
+// pass, and either what the sums over rows need (rows_ws), or per workgroup
+// the sums over its rows of every gradient (and of the loss) into its slot of
+// part; mlp_train_update: those sums in tile or workgroup order (the same
+// order) into the gradient buffers, then (adam) the Adam step and every copy
+// of each new parameter.
 constexpr int kTrainMaxLayers = kMlpMaxHidden + 2;
 constexpr int kTrainMaxGroups = 256;   // workgroups of one step (more tiles: each takes several)
 struct TrainArgs {
@@ -151,9 +152,12 @@ struct TrainArgs {
   int64_t off_b[kTrainMaxLayers] = {};
   int tiles = 0;                       // row tiles (train_tile_rows(width) rows each)
   int groups = 0;                      // workgroups (at most kTrainMaxGroups)
+  void* rows_ws = nullptr;             // train_rows_bytes: rows and sums as two kernels (part and zws unused)
 };
+struct AdamStep { int adam; float lr, b1, b2, eps, c1, c2; };   // adam = 0: gradients only
 int train_tile_rows(int width);
 int64_t train_zws_floats(int width, int nh);
+int64_t train_rows_bytes(int width, int nh, int64_t tiles);
 hipError_t mlp_train_grads(int width, const TrainArgs& a, hipStream_t s);
 // Per Adam segment: the packed copies of the parameter to refresh (NULL: none).
 // Plain data (copied to LDS by the update kernel); value-initialise on the host.
@@ -165,9 +169,8 @@ struct PackSeg {
   int nchunks, tchunks;
   float* bias;                         // contiguous hidden-layer biases
 };
-hipError_t mlp_train_update(const AdamSeg* segs, const PackSeg* pk, int nseg, int64_t total, const float* part,
-                            int groups, int64_t pstride, float* loss, int adam, float lr, float b1, float b2,
-                            float eps, float c1, float c2, hipStream_t s);
+hipError_t mlp_train_update(int width, const TrainArgs& a, const AdamSeg* segs, const PackSeg* pk, int nseg, float* loss,
+                            const AdamStep& ad, hipStream_t s);
 // sums[0..ld) += column sums of x [n][ld], sums[ld..2ld) += sums of squares
 // (FP64); clear: zero sums first.
 hipError_t mlp_moments(const float* x, int64_t n, int ld, double* sums, bool clear, hipStream_t s);

@@ -869,6 +869,13 @@ __device__ __forceinline__ void split_bf16(float v, bf16& hi, bf16& lo) {
   lo = bf16(v - float(hi));
 }
 
+// of silu(z); lo is the remainder of the unrounded product
+__device__ __forceinline__ void split_silu(float z, bf16& hi, bf16& lo) {
+  const float s = sigmoid(z);
+  hi = bf16(z * s);
+  lo = bf16(fmaf(z, s, -float(hi)));
+}
+
 // Sums over the R rows of nout outputs, by every thread of the workgroup: G
 // consecutive threads per output (G a power of two up to 8, as many as the
 // threads allow), each over R / G consecutive rows in order, combined by a
@@ -1136,7 +1143,7 @@ __global__ __launch_bounds__(64 * TrainShape<W>::NWV, 1) void train_k(const Trai
       for (int i = 0; i < 16; ++i) {
         const int fo = acc_feat(fw * FB + u, i, h);
         const float z = zl[u][i];
-        split_bf16(silu(z), ah_s[fo][rl], al_s[fo][rl]);
+        split_silu(z, ah_s[fo][rl], al_s[fo][rl]);
         split_bf16((g0 * whead[fo] + g1 * whead[W + fo]) * silu_grad(z), gh_s[fo][rl], gl_s[fo][rl]);
       }
     __syncthreads();
@@ -1265,15 +1272,679 @@ __global__ __launch_bounds__(64 * TrainShape<W>::NWV, 1) void train_k(const Trai
   if (threadIdx.x == 0) part[a.total] = loss_acc;
 }
 
-// Per parameter element: the workgroups' sums in workgroup order into the
-// gradient buffer; with adam, the step of adam_all and every copy of the new
-// value (operand copies, packed forward and transposed orders, contiguous
-// hidden biases).  Element total: the loss sum.  Padding elements get a zero
+// Element (r, c) of a segment: its gradient, and (ad.adam) the step of adam_all
+// and every copy of the new value (operand copies, packed forward and
+// transposed orders, contiguous hidden biases).  Padding elements have a zero
 // gradient and stay zero.
+// st: the element's state (element_state), which may be read well before gv is
+// known.
+struct AdamState { float m, v, w; };
+__device__ __forceinline__ AdamState element_state(const AdamSeg& sg, int r, int c, const AdamStep& ad) {
+  if (!ad.adam || r >= sg.mask_rows || c >= sg.mask_cols) return {0.0f, 0.0f, 0.0f};
+  const int64_t i = int64_t(r) * sg.cols + c;
+  return {sg.m[i], sg.v[i], sg.w[i]};
+}
+__device__ __forceinline__ void new_gradient(const AdamSeg& sg, const PackSeg& pq, int r, int c, float gv,
+                                             const AdamStep& ad, const AdamState& st) {
+  const int64_t i = int64_t(r) * sg.cols + c;
+  pq.grad[i] = gv;
+  if (!ad.adam) return;
+  float wi = 0.0f;
+  if (r < sg.mask_rows && c < sg.mask_cols) {
+    const float mi = ad.b1 * st.m + (1.0f - ad.b1) * gv;
+    const float vi = ad.b2 * st.v + (1.0f - ad.b2) * gv * gv;
+    sg.m[i] = mi;
+    sg.v[i] = vi;
+    wi = st.w - ad.lr * (mi * ad.c1) / (sqrtf(vi * ad.c2) + ad.eps);
+    sg.w[i] = wi;
+  }
+  if (sg.bf16_out) {
+    if (sg.wt) static_cast<bf16*>(sg.wt)[i] = bf16(wi);
+    if (sg.wtt) static_cast<bf16*>(sg.wtt)[size_t(c) * sg.rows + r] = bf16(wi);
+  } else {
+    if (sg.wt) static_cast<float*>(sg.wt)[i] = wi;
+    if (sg.wtt) static_cast<float*>(sg.wtt)[size_t(c) * sg.rows + r] = wi;
+  }
+  if (pq.hi) {
+    const int64_t t = pack_pos(r, c, pq.nchunks);
+    bf16 vh, vl;
+    split_bf16(wi, vh, vl);
+    static_cast<bf16*>(pq.hi)[t] = vh;
+    if (pq.lo) static_cast<bf16*>(pq.lo)[t] = vl;
+  }
+  if (pq.tr) static_cast<bf16*>(pq.tr)[pack_pos(c, r, pq.tchunks)] = bf16(wi);
+  if (pq.bias) pq.bias[c] = wi;
+}
+
+__device__ __forceinline__ void new_gradient(const AdamSeg& sg, const PackSeg& pq, int r, int c, float gv,
+                                             const AdamStep& ad) {
+  new_gradient(sg, pq, r, c, gv, ad, element_state(sg, r, c, ad));
+}
+
+// ------------------------------------------ training step, rows then sums
+// The step of train_k as two kernels with the sums over rows taken out of the
+// first: train_rows_k runs 32 rows per workgroup (128 or 64 in train_k, which
+// leaves most of the chip idle: 4096 rows are 32 workgroups of 16 waves, and
+// its layers are bound by the vector and LDS instructions of those 32 compute
+// units) and writes what the sums need, laid out as matrix operands;
+// train_sums_k has a workgroup per 32 x 32 block of a weight gradient, which
+// adds the row tiles up and steps the block's parameters.  Every sum keeps
+// train_k's order (its tiles of R rows, its 16-row products within them, its
+// groups of lanes), so the parameters are train_k's to the bit.  4096 rows of
+// the 18-128-128-128-2 network: 18 + 17 us (train_k and train_update_k 46 +
+// 10); a whole step with its gaps 49 us (69), of 4 x 256 76 us (139).  Bound
+// now by latency: the rows by a dozen dependent layers, barriers and LDS turns
+// of about 1 us each, the sums by 53 workgroups reading 0.5 - 1 MB each at 35 B
+// a cycle.
+//
+// A matrix [feature][row] in operand order: for each 16 rows and each 32
+// features 64 lanes x 8 values, lane l holding rows 8 (l / 32) .. + 7 of
+// feature l % 32.
+template <int W>
+struct RowsLayout {                               // in 16-byte units
+  using T = TrainShape<W>;
+  int64_t steps, mat;                             // 16-row steps; a matrix of W features
+  int nh;
+  __host__ __device__ RowsLayout(int64_t tiles, int nh_) : steps(tiles * (T::R / 16)), mat(steps * T::NB * 64), nh(nh_) {}
+  __host__ __device__ int64_t h(int q) const { return q * mat; }                       // layer inputs, q = 0 .. nh - 1
+  __host__ __device__ int64_t g(int q) const { return (nh + q) * mat; }                // gradients, q = 0 .. nh
+  __host__ __device__ int64_t g_lo() const { return (2 * nh + 1) * mat; }              // low parts of the first layer's
+  __host__ __device__ int64_t x_hi() const { return (2 * nh + 2) * mat; }              // inputs, one block of 32
+  __host__ __device__ int64_t x_lo() const { return x_hi() + steps * 64; }
+  // floats: sums over 8 rows [row / 8][W] of each layer's G and of the heads'
+  // products, the heads' gradients [2][row], the loss per 32 rows, and the
+  // pre-activations where the LDS does not hold them
+  __host__ __device__ int64_t bias(int q) const { return x_lo() + steps * 64 + q * (steps * W / 2); }
+  __host__ __device__ int64_t heads(int j) const { return bias(nh + 1 + j); }
+  __host__ __device__ int64_t ghead() const { return heads(2); }
+  __host__ __device__ int64_t loss() const { return ghead() + steps * 8; }
+  __host__ __device__ int64_t z() const { return loss() + (steps / 2 + 3) / 4; }
+  __host__ __device__ static constexpr int z_lds(int nh) {   // bytes, 0: too many
+    return nh * T::NB * 4096 <= 98304 ? nh * T::NB * 4096 : 0;
+  }
+  __host__ __device__ int64_t size() const { return z() + (z_lds(nh) ? 0 : steps * 4 * W * int64_t(nh)); }
+};
+
+int64_t train_rows_bytes(int width, int nh, int64_t tiles) {
+  return 16 * (width == 128 ? RowsLayout<128>(tiles, nh).size() : RowsLayout<256>(tiles, nh).size());
+}
+
+// A wave's 32 rows x 32 features (element i of lane l: row l % 32, feature
+// acc_feat(0, i, l / 32)) to 16-byte units of operand order; one wave's tile.
+struct Turn { bf16 t[32][40]; };                  // [feature][row], rows of 80 bytes
+__device__ __forceinline__ void turn_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+template <class V>
+__device__ __forceinline__ void turn(Turn& tt, V value, bf16x8_t (&out)[2]) {   // of the 32 rows' two 16-row steps
+  const int lane = threadIdx.x & 63, h = lane >> 5, r = lane & 31;
+  turn_sync();                                    // the previous matrix has been read
+#pragma unroll
+  for (int i = 0; i < 16; ++i) tt.t[acc_feat(0, i, h)][r] = value(i);
+  turn_sync();
+#pragma unroll
+  for (int k = 0; k < 2; ++k) out[k] = *reinterpret_cast<const bf16x8_t*>(&tt.t[r][16 * k + 8 * h]);
+}
+__device__ __forceinline__ void store_steps(bf16x8_t* out, const bf16x8_t (&v)[2], int nb, int b, int64_t rg) {
+#pragma unroll
+  for (int k = 0; k < 2; ++k) out[((2 * rg + k) * nb + b) * 64 + (threadIdx.x & 63)] = v[k];
+}
+
+// Over 8 rows, in the order of sum8: hi + lo, or that times a.
+__device__ __forceinline__ float add8(bf16x8_t hi, bf16x8_t lo) {
+  float s = 0.0f;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) s = s + (float(hi[k]) + float(lo[k]));
+  return s;
+}
+__device__ __forceinline__ float dot8(const float* a, bf16x8_t hi, bf16x8_t lo) {
+  float s = 0.0f;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) s = fmaf(a[k], float(hi[k]) + float(lo[k]), s);
+  return s;
+}
+
+template <int W, int NPART, int KIND, bool XROWS>
+__global__ __launch_bounds__(64 * TrainShape<W>::NF, 1) void train_rows_k(const TrainArgs a) {
+  using T = TrainShape<W>;
+  constexpr int NB = T::NB, NC = T::NC, FB = T::FB, NF = T::NF;
+  // the layer's input or gradient, a row's features together: what a lane
+  // needs of a 16-feature chunk are two 8-byte reads, and 4 features of an
+  // accumulator one 8-byte write
+  typedef bf16 bf16x4 __attribute__((ext_vector_type(4)));
+  __shared__ __attribute__((aligned(16))) bf16 rows_s[32][W + 8];
+  __shared__ __attribute__((aligned(16))) Turn turn_s[NF];
+  __shared__ float hpart[NF][32][2];
+  __shared__ __attribute__((aligned(16))) float ghead_s[NF][2][32];
+  extern __shared__ float z_s[];                    // [layer][wave][block][16][64] where it fits
+  const int lane = threadIdx.x & 63, h = lane >> 5, rl = lane & 31;
+  const int fw = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+  const int nh = a.nh;
+  const int64_t rg = blockIdx.x;
+  const RowsLayout<W> lay(a.tiles, nh);
+  bf16x8_t* const ws = static_cast<bf16x8_t*>(a.rows_ws);
+  const bool z_in_lds = RowsLayout<W>::z_lds(nh) != 0;
+  float* const zw = reinterpret_cast<float*>(ws + lay.z()) + (rg * NF + fw) * int64_t(nh) * FB * 16 * 64 + lane;
+  float* const zs = z_s + fw * nh * FB * 16 * 64 + lane;
+  auto keep_z = [&](int q, int u, auto value) {
+    const int at = (q * FB + u) * 16 * 64;
+    if (z_in_lds) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) zs[at + i * 64] = value(i);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) zw[at + i * 64] = value(i);
+    }
+  };
+  Turn& tt = turn_s[fw];
+  auto put_rows = [&](int u, auto value) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      bf16x4 v;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = value(4 * j + k);
+      *reinterpret_cast<bf16x4*>(&rows_s[rl][32 * (fw * FB + u) + 8 * j + 4 * h]) = v;
+    }
+  };
+  auto get_chunk = [&](int c) {
+    const bf16x4 lo = *reinterpret_cast<const bf16x4*>(&rows_s[rl][16 * c + 4 * h]);
+    const bf16x4 hi = *reinterpret_cast<const bf16x4*>(&rows_s[rl][16 * c + 8 + 4 * h]);
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+  };
+
+  const bf16x8_t* w0h = static_cast<const bf16x8_t*>(a.w0hi) + lane;
+  const bf16x8_t* w0l = static_cast<const bf16x8_t*>(a.w0lo) + lane;
+  const bf16x8_t* wh = static_cast<const bf16x8_t*>(a.wh) + lane;
+  const bf16x8_t* wht = static_cast<const bf16x8_t*>(a.wht) + lane;
+  // A layer's weights and biases are on their way while the layer before it
+  // is computed (one wave per SIMD has the registers, and the barriers keep the
+  // compiler from asking early): every layer would wait for the L2 otherwise.
+  bf16x8_t wn[FB][NC];
+  float bn[FB][16];
+  auto want = [&](const bf16x8_t* w) {
+#pragma unroll
+    for (int u = 0; u < FB; ++u)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) wn[u][c] = w[((fw * FB + u) * NC + c) * 64];
+  };
+  auto want_bias = [&](const float* b) {
+#pragma unroll
+    for (int u = 0; u < FB; ++u)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) bn[u][i] = b[acc_feat(fw * FB + u, i, h)];
+  };
+  bf16x8_t wa[FB][2], wb[FB][2];
+#pragma unroll
+  for (int u = 0; u < FB; ++u)
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      wa[u][c] = w0h[((fw * FB + u) * 2 + c) * 64];
+      wb[u][c] = w0l[((fw * FB + u) * 2 + c) * 64];
+    }
+  want_bias(a.b0);
+  const int64_t r = rg * 32 + rl;
+  const bool valid = r < a.n;
+  float f[kMlpMaxIn];
+  float yv;
+  if constexpr (XROWS) {
+    const int64_t rr = r < a.rows ? r : a.rows - 1;
+#pragma unroll
+    for (int k = 0; k < kMlpMaxIn; ++k) f[k] = a.x[rr * kMlpMaxIn + k];
+    yv = a.y[rr];
+  } else {
+    const int64_t rr = valid ? r : a.n - 1;
+    const int64_t j = shuffled(a.sh, a.pos0 + rr);
+    const int64_t e = j % a.nevt;
+    const int c = int(j / a.nevt);
+    double p[NPART * 4];
+    load_event<NPART>(a.mom, e, p);
+    const float card[3] = {a.cpar[3 * c], a.cpar[3 * c + 1], a.cpar[3 * c + 2]};
+    feature_row<NPART, KIND>(a.fm, p, card, f);
+    standardise(f, a.mean, a.istd);
+    yv = a.ygrid[j];
+  }
+  // this lane's half of the inputs, as the fused inference kernel takes it
+  const unsigned int pick = h ? ~0u : 0u;
+  bf16x8_t xh[2], xl[2];
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      const int k = 16 * c + 8 * (s >> 2) + (s & 3);
+      const unsigned int u0 = __float_as_uint(f[k]), u1 = __float_as_uint(f[k + 4]);
+      bf16 vh, vl;
+      split_bf16(__uint_as_float(u0 ^ ((u0 ^ u1) & pick)), vh, vl);
+      xh[c][s] = vh;
+      xl[c][s] = vl;
+    }
+  if (fw == 0) {
+    bf16x8_t v[2];
+    turn(tt, [&](int i) { return xh[i >> 3][i & 7]; }, v);
+    store_steps(ws + lay.x_hi(), v, 1, 0, rg);
+    turn(tt, [&](int i) { return xl[i >> 3][i & 7]; }, v);
+    store_steps(ws + lay.x_lo(), v, 1, 0, rg);
+  }
+  auto store_h = [&](int q, int u, auto value) {
+    bf16x8_t v[2];
+    turn(tt, value, v);
+    store_steps(ws + lay.h(q), v, NB, fw * FB + u, rg);
+  };
+  // 8-row sums of this lane's feature of block u: [row / 8][W]
+  auto store_sums = [&](int64_t at, int u, int k, float v) {
+    reinterpret_cast<float*>(ws + at)[((2 * rg + k) * 2 + h) * W + 32 * (fw * FB + u) + rl] = v;
+  };
+  auto store_g = [&](int q, int u, auto hi, auto lo) {
+    bf16x8_t vh[2], vl[2];
+    turn(tt, hi, vh);
+    store_steps(ws + lay.g(q), vh, NB, fw * FB + u, rg);
+    turn(tt, lo, vl);
+    if (q == 0) store_steps(ws + lay.g_lo(), vl, NB, fw * FB + u, rg);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) store_sums(lay.bias(q), u, k, add8(vh[k], vl[k]));
+  };
+
+  // ------------------------------------------------------------ forward
+#pragma unroll
+  for (int u = 0; u < FB; ++u) {
+    const int b = fw * FB + u;
+    f32x16_t acc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = bn[u][i];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      acc = mfma_bf16(wa[u][c], xh[c], acc);
+      acc = mfma_bf16(wa[u][c], xl[c], acc);
+      acc = mfma_bf16(wb[u][c], xh[c], acc);
+    }
+    bf16 v[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = bf16(silu(acc[i]));
+    put_rows(u, [&](int i) { return v[i]; });
+    keep_z(0, u, [&](int i) { return acc[i]; });
+    store_h(0, u, [&](int i) { return v[i]; });
+  }
+  want(wh);
+  want_bias(a.bh);
+  __syncthreads();
+  float w_mu[FB][16], w_sg[FB][16];                     // the heads' weights, as early
+#pragma unroll
+  for (int u = 0; u < FB; ++u)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int fo = acc_feat(fw * FB + u, i, h);
+      w_mu[u][i] = a.whead[fo];
+      w_sg[u][i] = a.whead[W + fo];
+    }
+  float mu = 0.0f, sg = 0.0f;
+  float zl[FB][16];                                     // the last hidden layer's pre-activations
+  for (int q = 0; q < nh; ++q) {
+    f32x16_t acc[FB];
+#pragma unroll
+    for (int u = 0; u < FB; ++u)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[u][i] = bn[u][i];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const bf16x8_t xc = get_chunk(c);
+#pragma unroll
+      for (int u = 0; u < FB; ++u) acc[u] = mfma_bf16(wn[u][c], xc, acc[u]);
+    }
+    const bool last = q + 1 == nh;
+    want(last ? wht + size_t(nh - 1) * NB * NC * 64 : wh + size_t(q + 1) * NB * NC * 64);
+    if (!last) want_bias(a.bh + size_t(q + 1) * W);
+#pragma unroll
+    for (int u = 0; u < FB; ++u)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) zl[u][i] = acc[u][i];
+    if (last) break;
+    bf16 v[FB][16];
+#pragma unroll
+    for (int u = 0; u < FB; ++u)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) v[u][i] = bf16(silu(zl[u][i]));
+    __syncthreads();                                    // every wave has read this layer's inputs
+#pragma unroll
+    for (int u = 0; u < FB; ++u) put_rows(u, [&](int i) { return v[u][i]; });
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < FB; ++u) {
+      keep_z(q + 1, u, [&](int i) { return zl[u][i]; });
+      store_h(q + 1, u, [&](int i) { return v[u][i]; });
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < FB; ++u)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {                      // the last hidden layer feeds the FP32 heads
+      const float v = silu(zl[u][i]);
+      mu = fmaf(v, w_mu[u][i], mu);
+      sg = fmaf(v, w_sg[u][i], sg);
+    }
+  mu += __shfl_xor(mu, 32);
+  sg += __shfl_xor(sg, 32);
+  if (lane < 32) {
+    hpart[fw][rl][0] = mu;
+    hpart[fw][rl][1] = sg;
+  }
+  __syncthreads();                                      // partial heads written; the inputs read
+  mu = 0.0f;
+  sg = 0.0f;
+#pragma unroll
+  for (int k = 0; k < NF; ++k) {
+    mu += hpart[k][rl][0];
+    sg += hpart[k][rl][1];
+  }
+  mu += a.bhead[0];
+  sg += a.bhead[1];
+
+  // ---------------------------------------------- loss and its gradient
+  float g0 = 0.0f, g1 = 0.0f, lrow = 0.0f;
+  if (valid) {
+    const float s = fmaxf(sg, -15.0f);                  // log-error head clamped as loss_grad does
+    const float res = (yv - a.ym) / a.ys - mu;
+    const float e2 = __expf(-2.0f * s);
+    const float inv = 1.0f / float(a.n);
+    g0 = -res * inv;
+    g1 = sg > -15.0f ? a.lambda * (1.0f - res * res * e2) * inv : 0.0f;
+    lrow = 0.5f * res * res + a.lambda * (0.5f * res * res * e2 + s);
+  }
+  if (fw == 0) {
+    float lw = lane < 32 ? lrow : 0.0f;
+    for (int off = 32; off > 0; off >>= 1) lw += __shfl_down(lw, off);
+    if (lane == 0) reinterpret_cast<float*>(ws + lay.loss())[rg] = lw;
+    if (lane < 32) {
+      float* gh = reinterpret_cast<float*>(ws + lay.ghead());
+      gh[r] = g0;
+      gh[lay.steps * 16 + r] = g1;
+    }
+  }
+  if (lane < 32) {                                      // this wave's copy
+    ghead_s[fw][0][rl] = g0;
+    ghead_s[fw][1][rl] = g1;
+  }
+  // the heads' FP32 input and the gradient of the last hidden layer's
+  // pre-activation, hi / lo, this wave's blocks
+  bf16 vh[16], vl[16], gh[FB][16], gl[FB][16];
+#pragma unroll
+  for (int u = 0; u < FB; ++u) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const float z = zl[u][i];
+      split_silu(z, vh[i], vl[i]);
+      split_bf16((g0 * w_mu[u][i] + g1 * w_sg[u][i]) * silu_grad(z), gh[u][i], gl[u][i]);
+    }
+    put_rows(u, [&](int i) { return gh[u][i]; });
+    bf16x8_t xh8[2], xl8[2];
+    turn(tt, [&](int i) { return vh[i]; }, xh8);
+    turn(tt, [&](int i) { return vl[i]; }, xl8);
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+        store_sums(lay.heads(j), u, k, dot8(&ghead_s[fw][j][16 * k + 8 * h], xh8[k], xl8[k]));
+  }
+  __syncthreads();
+
+  // ------------------------------------------------------------ backward
+  for (int l = nh; l >= 1; --l) {                       // (bf16(G) W) SiLU'(z), the layer below's G
+    float zv[FB][16];
+    if (!z_in_lds)
+#pragma unroll
+      for (int u = 0; u < FB; ++u)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) zv[u][i] = zw[((l - 1) * FB + u) * 16 * 64 + i * 64];
+    f32x16_t acc[FB] = {};
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const bf16x8_t gc = get_chunk(c);
+#pragma unroll
+      for (int u = 0; u < FB; ++u) acc[u] = mfma_bf16(wn[u][c], gc, acc[u]);
+    }
+    if (l > 1) want(wht + size_t(l - 2) * NB * NC * 64);
+#pragma unroll
+    for (int u = 0; u < FB; ++u)                        // this layer's G, while the products run
+      store_g(l, u, [&](int i) { return gh[u][i]; }, [&](int i) { return gl[u][i]; });
+    if (z_in_lds)
+#pragma unroll
+      for (int u = 0; u < FB; ++u)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) zv[u][i] = zs[((l - 1) * FB + u) * 16 * 64 + i * 64];
+#pragma unroll
+    for (int u = 0; u < FB; ++u)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) split_bf16(acc[u][i] * silu_grad(zv[u][i]), gh[u][i], gl[u][i]);
+    __syncthreads();                                    // every read of this layer's G is done
+#pragma unroll
+    for (int u = 0; u < FB; ++u) put_rows(u, [&](int i) { return gh[u][i]; });
+    __syncthreads();
+  }
+#pragma unroll
+  for (int u = 0; u < FB; ++u) store_g(0, u, [&](int i) { return gh[u][i]; }, [&](int i) { return gl[u][i]; });
+}
+
+// Sums over the row tiles in tile order: each of the 8 waves of a workgroup
+// takes 2 tiles a round, values(t, t', v, v') giving the wave's 64 NV sums over
+// the rows of each, and the threads add a round's tiles up.  Thread t ends
+// with sum e = t + 512 k in s[k], value e / 64 of lane e % 64.
+constexpr int kSumWaves = 8, kSumTiles = 2 * kSumWaves;
+template <int NV, class V>
+__device__ __forceinline__ void sum_tiles(float (*buf)[1024], int tiles, float (&s)[2], V values) {
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+  s[0] = s[1] = 0.0f;
+  for (int t0 = 0; t0 < tiles; t0 += kSumTiles) {
+    float v[2][NV];
+    const int ta = t0 + wv, tb = ta + kSumWaves;        // past the last tile: that one again, not added
+    values(ta < tiles ? ta : tiles - 1, tb < tiles ? tb : tiles - 1, v[0], v[1]);
+    __syncthreads();                                    // the previous round has been added
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+      for (int i = 0; i < NV; ++i) buf[wv + kSumWaves * k][i * 64 + lane] = v[k][i];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int e = int(threadIdx.x) + 64 * kSumWaves * k;
+      if (e < NV * 64)
+#pragma unroll
+        for (int w = 0; w < kSumTiles; ++w)
+          if (t0 + w < tiles) s[k] += buf[w][e];
+    }
+  }
+}
+// values of one tile at a time
+template <int NV, class V>
+__device__ __forceinline__ void sum_each_tile(float (*buf)[1024], int tiles, float (&s)[2], V values) {
+  sum_tiles<NV>(buf, tiles, s, [&](int ta, int tb, float (&va)[NV], float (&vb)[NV]) {
+    values(ta, va);
+    values(tb, vb);
+  });
+}
+
+// Bias and head sums over a tile as group_sums takes them over train_k's
+// workgroup: G lane groups of R / G rows, in 8-row pieces, joined by a
+// butterfly.  rows8(r0): the sum over rows r0 .. r0 + 7 of the tile.
+template <int R, int G, class P>
+__device__ __forceinline__ float tile_sum(int h, P rows8) {
+  constexpr int SPAN = R / G, PER = G > 1 ? G / 2 : 1;  // groups per half wave (G = 1: each half has its own sum)
+  float g[PER];
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const int first = (G > 1 ? h * PER + j : 0) * SPAN;
+    g[j] = 0.0f;
+#pragma unroll
+    for (int r0 = 0; r0 < SPAN; r0 += 8) g[j] += rows8(first + r0);
+  }
+#pragma unroll
+  for (int m = 1; m < PER; m <<= 1)
+#pragma unroll
+    for (int j = 0; j < PER; j += 2 * m) g[j] += g[j + m];
+  if constexpr (G > 1) g[0] += __shfl_xor(g[0], 32);
+  return g[0];
+}
+template <int W>
+constexpr int sum_groups(int outputs) {                 // group_sums' G
+  int G = 1;
+  while (G < 8 && G * 8 < TrainShape<W>::R && outputs * G * 2 <= 64 * TrainShape<W>::NWV) G *= 2;
+  return G;
+}
+
+template <int W> constexpr int sums_blocks(int nh) {
+  constexpr int NB = W / 32;
+  return nh * NB * NB + NB + (nh + 1) * NB + NB + 1;
+}
+
+template <int W>
+__global__ __launch_bounds__(64 * kSumWaves) void train_sums_k(const TrainArgs a, const AdamSeg* __restrict__ segs,
+                                                              const PackSeg* __restrict__ pk, float* __restrict__ loss,
+                                                              const AdamStep ad) {
+  using T = TrainShape<W>;
+  constexpr int NB = T::NB, R = T::R, KS = R / 16;
+  constexpr int GB = sum_groups<W>(W), GH = sum_groups<W>(2 * W + 2);
+  __shared__ float buf[kSumTiles][1024];
+  const int lane = threadIdx.x & 63, h = lane >> 5, tid = int(threadIdx.x);
+  const int nh = a.nh, head = nh + 1;
+  const RowsLayout<W> lay(a.tiles, nh);
+  const bf16x8_t* ws = static_cast<const bf16x8_t*>(a.rows_ws);
+  const float* ghead = reinterpret_cast<const float*>(ws + lay.ghead());
+  const float* rloss = reinterpret_cast<const float*>(ws + lay.loss());
+  float s[2];
+  int job = int(blockIdx.x);
+  if (job < NB) {                                       // first layer's weights, outputs of block job
+    const bf16x8_t *gh = ws + lay.g(0) + job * 64 + lane, *gl = ws + lay.g_lo() + job * 64 + lane;
+    const bf16x8_t *xh = ws + lay.x_hi() + lane, *xl = ws + lay.x_lo() + lane;
+    const AdamSeg sg = segs[0];
+    AdamState st[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+      st[k] = element_state(sg, acc_feat(job, (tid + 64 * kSumWaves * k) >> 6, h), lane & 31, ad);
+    sum_each_tile<16>(buf, a.tiles, s, [&](int t, float (&v)[16]) {
+      f32x16_t acc = {};
+      bf16x8_t m[4][KS];
+#pragma unroll
+      for (int k = 0; k < KS; ++k) {
+        const int64_t step = int64_t(t) * KS + k, at = step * NB * 64;
+        m[0][k] = gh[at];
+        m[1][k] = xh[step * 64];
+        m[2][k] = xl[step * 64];
+        m[3][k] = gl[at];
+      }
+      __builtin_amdgcn_sched_barrier(0);                // every load on its way
+#pragma unroll
+      for (int k = 0; k < KS; ++k) {
+        acc = mfma_bf16(m[0][k], m[1][k], acc);
+        acc = mfma_bf16(m[0][k], m[2][k], acc);
+        acc = mfma_bf16(m[3][k], m[1][k], acc);
+      }
+#pragma unroll
+      for (int i = 0; i < 16; ++i) v[i] = acc[i];
+    });
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int e = tid + 64 * kSumWaves * k, c = lane & 31;
+      new_gradient(sg, pk[0], acc_feat(job, e >> 6, h), c, c < sg.mask_cols ? s[k] : 0.0f, ad, st[k]);
+    }
+    return;
+  }
+  job -= NB;
+  if (job < nh * NB * NB) {                             // hidden weights, block (ob, ib) of layer l
+    const int l = 1 + job / (NB * NB), ob = job / NB % NB, ib = job % NB;
+    const bf16x8_t *g = ws + lay.g(l) + ob * 64 + lane, *x = ws + lay.h(l - 1) + ib * 64 + lane;
+    const AdamSeg sg = segs[2 * l];
+    AdamState st[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+      st[k] = element_state(sg, acc_feat(ob, (tid + 64 * kSumWaves * k) >> 6, h), 32 * ib + (lane & 31), ad);
+    sum_tiles<16>(buf, a.tiles, s, [&](int ta, int tb, float (&va)[16], float (&vb)[16]) {
+      bf16x8_t m[4][KS];
+#pragma unroll
+      for (int k = 0; k < KS; ++k) {
+        const int64_t at = (int64_t(ta) * KS + k) * NB * 64, bt = (int64_t(tb) * KS + k) * NB * 64;
+        m[0][k] = g[at];
+        m[1][k] = x[at];
+        m[2][k] = g[bt];
+        m[3][k] = x[bt];
+      }
+      __builtin_amdgcn_sched_barrier(0);                // every load on its way
+      f32x16_t acc = {}, bcc = {};
+#pragma unroll
+      for (int k = 0; k < KS; ++k) {
+        acc = mfma_bf16(m[0][k], m[1][k], acc);
+        bcc = mfma_bf16(m[2][k], m[3][k], bcc);
+      }
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        va[i] = acc[i];
+        vb[i] = bcc[i];
+      }
+    });
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int e = tid + 64 * kSumWaves * k;
+      new_gradient(sg, pk[2 * l], acc_feat(ob, e >> 6, h), 32 * ib + (lane & 31), s[k], ad, st[k]);
+    }
+    return;
+  }
+  job -= nh * NB * NB;
+  if (job < (nh + 1) * NB) {                            // biases, block ob of layer l
+    const int l = job / NB, ob = job % NB;
+    const float* p = reinterpret_cast<const float*>(ws + lay.bias(l)) + 32 * ob + (lane & 31);
+    sum_each_tile<1>(buf, a.tiles, s, [&](int t, float (&v)[1]) {
+      v[0] = tile_sum<R, GB>(h, [&](int r0) { return p[(int64_t(t) * R + r0) / 8 * W]; });
+    });
+    if (tid < 32) new_gradient(segs[2 * l + 1], pk[2 * l + 1], 0, 32 * ob + tid, s[0], ad);
+    return;
+  }
+  job -= (nh + 1) * NB;
+  if (job < NB) {                                       // the heads' weights, inputs of block job
+    const float* p = reinterpret_cast<const float*>(ws + lay.heads(0)) + 32 * job + (lane & 31);
+    const int64_t next = (lay.heads(1) - lay.heads(0)) * 4;
+    if constexpr (GH > 1) {                             // a half wave per lane group, both heads
+      sum_each_tile<2>(buf, a.tiles, s, [&](int t, float (&v)[2]) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          v[j] = tile_sum<R, GH>(h, [&](int r0) { return p[j * next + (int64_t(t) * R + r0) / 8 * W]; });
+      });
+      if (tid < 128 && h == 0) new_gradient(segs[2 * head], pk[2 * head], tid >> 6, 32 * job + lane, s[0], ad);
+    } else {                                            // a half wave per head
+      sum_each_tile<1>(buf, a.tiles, s, [&](int t, float (&v)[1]) {
+        v[0] = tile_sum<R, 1>(h, [&](int r0) { return p[h * next + (int64_t(t) * R + r0) / 8 * W]; });
+      });
+      if (tid < 64) new_gradient(segs[2 * head], pk[2 * head], h, 32 * job + (lane & 31), s[0], ad);
+    }
+    for (int e = 64 + tid; e < 32 * 32; e += 64 * kSumWaves)   // padding rows
+      new_gradient(segs[2 * head], pk[2 * head], e >> 5, 32 * job + (e & 31), 0.0f, ad);
+    return;
+  }
+  // the heads' biases (lane groups on lanes 0 and 32 of two values) and the loss
+  sum_each_tile<3>(buf, a.tiles, s, [&](int t, float (&v)[3]) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const float* g = ghead + (j ? lay.steps * 16 : 0) + int64_t(t) * R;
+      v[j] = tile_sum<R, GH>(h, [&](int r0) {
+        float p = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) p += g[r0 + k];
+        return p;
+      });
+    }
+    float t0 = 0.0f;
+#pragma unroll
+    for (int k = 0; k < T::RG; ++k) t0 += rloss[int64_t(t) * T::RG + k];
+    v[2] = t0;
+  });
+  if (lane == 0 && tid < 128) new_gradient(segs[2 * head + 1], pk[2 * head + 1], 0, tid >> 6, s[0], ad);
+  if (tid == 128) *loss = s[0];
+  if (tid >= 2 && tid < 32) new_gradient(segs[2 * head + 1], pk[2 * head + 1], 0, tid, 0.0f, ad);
+}
+
+// Per parameter element: the workgroups' sums in workgroup order
+// (new_gradient).  Element total: the loss sum.
 __global__ __launch_bounds__(256) void train_update_k(const AdamSeg* __restrict__ segs, const PackSeg* __restrict__ pk,
                                                       int nseg, int64_t total, const float* __restrict__ part,
-                                                      int groups, int64_t pstride, float* __restrict__ loss, int adam,
-                                                      float lr, float b1, float b2, float eps, float c1, float c2) {
+                                                      int groups, int64_t pstride, float* __restrict__ loss,
+                                                      const AdamStep ad) {
   // the segment tables in LDS: the lookup below reads them in a dependent
   // chain, which from global memory costs a round trip per segment
   __shared__ AdamSeg s_seg[2 * kTrainMaxLayers];
@@ -1309,33 +1980,7 @@ __global__ __launch_bounds__(256) void train_update_k(const AdamSeg* __restrict_
       for (int k = 0; k < 32; ++k) gv += v[k];
     }
   }
-  pq.grad[i] = gv;
-  if (!adam) return;
-  float wi = 0.0f;
-  if (used) {
-    const float mi = b1 * sg.m[i] + (1.0f - b1) * gv;
-    const float vi = b2 * sg.v[i] + (1.0f - b2) * gv * gv;
-    sg.m[i] = mi;
-    sg.v[i] = vi;
-    wi = sg.w[i] - lr * (mi * c1) / (sqrtf(vi * c2) + eps);
-    sg.w[i] = wi;
-  }
-  if (sg.bf16_out) {
-    if (sg.wt) static_cast<bf16*>(sg.wt)[i] = bf16(wi);
-    if (sg.wtt) static_cast<bf16*>(sg.wtt)[size_t(c) * sg.rows + r] = bf16(wi);
-  } else {
-    if (sg.wt) static_cast<float*>(sg.wt)[i] = wi;
-    if (sg.wtt) static_cast<float*>(sg.wtt)[size_t(c) * sg.rows + r] = wi;
-  }
-  if (pq.hi) {
-    const int64_t t = pack_pos(r, c, pq.nchunks);
-    bf16 vh, vl;
-    split_bf16(wi, vh, vl);
-    static_cast<bf16*>(pq.hi)[t] = vh;
-    if (pq.lo) static_cast<bf16*>(pq.lo)[t] = vl;
-  }
-  if (pq.tr) static_cast<bf16*>(pq.tr)[pack_pos(c, r, pq.tchunks)] = bf16(wi);
-  if (pq.bias) pq.bias[c] = wi;
+  new_gradient(sg, pq, r, c, gv, ad);
 }
 
 // ----------------------------------------------------------------- launchers
@@ -1562,19 +2207,28 @@ hipError_t mlp_infer(int width, const InferArgs& a, hipStream_t s) {
 
 template <int W>
 static hipError_t train_launch(const TrainArgs& a, hipStream_t s) {
-  const dim3 g(unsigned(a.groups)), b(64 * TrainShape<W>::NWV);
+  const bool rows = a.rows_ws != nullptr;
+  const dim3 g(unsigned(rows ? a.tiles * TrainShape<W>::RG : a.groups));
+  const dim3 b(64 * (rows ? TrainShape<W>::NF : TrainShape<W>::NWV));
+  const int lds = rows ? RowsLayout<W>::z_lds(a.nh) : 0;
+  void (*k)(const TrainArgs);
   if (a.x)
-    hipLaunchKernelGGL((train_k<W, 4, kFeatRaw, true>), g, b, 0, s, a);
+    k = rows ? train_rows_k<W, 4, kFeatRaw, true> : train_k<W, 4, kFeatRaw, true>;
   else if (a.fm.npart == 4 && a.fm.kind == kFeatRaw)
-    hipLaunchKernelGGL((train_k<W, 4, kFeatRaw, false>), g, b, 0, s, a);
+    k = rows ? train_rows_k<W, 4, kFeatRaw, false> : train_k<W, 4, kFeatRaw, false>;
   else if (a.fm.npart == 4)
-    hipLaunchKernelGGL((train_k<W, 4, kFeatPhys, false>), g, b, 0, s, a);
+    k = rows ? train_rows_k<W, 4, kFeatPhys, false> : train_k<W, 4, kFeatPhys, false>;
   else if (a.fm.npart == 5 && a.fm.kind == kFeatRaw)
-    hipLaunchKernelGGL((train_k<W, 5, kFeatRaw, false>), g, b, 0, s, a);
+    k = rows ? train_rows_k<W, 5, kFeatRaw, false> : train_k<W, 5, kFeatRaw, false>;
   else if (a.fm.npart == 5)
-    hipLaunchKernelGGL((train_k<W, 5, kFeatPhys, false>), g, b, 0, s, a);
+    k = rows ? train_rows_k<W, 5, kFeatPhys, false> : train_k<W, 5, kFeatPhys, false>;
   else
     return hipErrorInvalidValue;
+  if (lds > 0) {                                          // beyond 64 KB the kernel has to ask
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(k, g, b, unsigned(lds), s, a);
   return hipGetLastError();
 }
 
@@ -1588,13 +2242,22 @@ hipError_t mlp_train_grads(int width, const TrainArgs& a, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
-hipError_t mlp_train_update(const AdamSeg* segs, const PackSeg* pk, int nseg, int64_t total, const float* part,
-                            int groups, int64_t pstride, float* loss, int adam, float lr, float b1, float b2,
-                            float eps, float c1, float c2, hipStream_t s) {
-  if (!segs || !pk || nseg < 1 || nseg > 2 * kTrainMaxLayers || total < 1 || groups < 1 || pstride <= total)
+hipError_t mlp_train_update(int width, const TrainArgs& a, const AdamSeg* segs, const PackSeg* pk, int nseg, float* loss,
+                            const AdamStep& ad, hipStream_t s) {
+  if (!segs || !pk || nseg != 2 * (a.nh + 2) || nseg > 2 * kTrainMaxLayers || a.total < 1 || a.groups < 1)
     return hipErrorInvalidValue;
-  hipLaunchKernelGGL(train_update_k, dim3(blocks_for(total + 1)), dim3(256), 0, s, segs, pk, nseg, total, part, groups,
-                     pstride, loss, adam, lr, b1, b2, eps, c1, c2);
+  if (a.rows_ws) {
+    if (width == 128)
+      hipLaunchKernelGGL(train_sums_k<128>, dim3(sums_blocks<128>(a.nh)), dim3(64 * kSumWaves), 0, s, a, segs, pk, loss, ad);
+    else if (width == 256)
+      hipLaunchKernelGGL(train_sums_k<256>, dim3(sums_blocks<256>(a.nh)), dim3(64 * kSumWaves), 0, s, a, segs, pk, loss, ad);
+    else
+      return hipErrorInvalidValue;
+  } else {
+    if (a.pstride <= a.total) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(train_update_k, dim3(blocks_for(a.total + 1)), dim3(256), 0, s, segs, pk, nseg, a.total, a.part,
+                       a.groups, a.pstride, loss, ad);
+  }
   return hipGetLastError();
 }
 

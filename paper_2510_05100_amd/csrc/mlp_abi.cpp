@@ -223,6 +223,7 @@ rwgt_mlp::~rwgt_mlp() {
   for (void* p : params) hipFree(p);
   if (tr_part) hipFree(tr_part);
   if (tr_zws) hipFree(tr_zws);
+  if (tr_rows) hipFree(tr_rows);
 }
 
 extern "C" {

@@ -39,6 +39,8 @@ struct rwgt_mlp {
   // sums and pre-activation workspace
   rwgt::PackSeg* pack_segs = nullptr;
   float *tr_part = nullptr, *tr_zws = nullptr;
+  void* tr_rows = nullptr;                                // rows of a training step as matrices
+  int64_t tr_rows_bytes = 0;
   int tr_groups = 0;                                      // workgroup slots allocated
   int64_t tr_pstride = 0;
   // batch workspace
