@@ -3,8 +3,7 @@
 One step = one rwgt_eval over the whole g g -> t t~ g g workload: 1e6 RAMBO
 events (sqrt(s) uniform in [500, 2000] GeV, massive tops, gluon cuts), the
 original card (alpha_s = 0.118) as normaliser and one new card
-(alpha_s = 0.130): ingest of the momenta, |M|^2 under both cards for every
-event, and w' = (w / |M|^2) * |M'|^2.  Inputs are resident in HBM before the
+(alpha_s = 0.130): |M|^2 under both cards for every event, and w' = (w / |M|^2) * |M'|^2.  Inputs are resident in HBM before the
 timed region.  The FP64 path gives ``value``; the mixed path (float
 amplitudes) is timed the same way and reported under ``mixed``.  Both carry
 the maximum relative error of w' against the exact ratio (0.130/0.118)^4 over
@@ -35,7 +34,13 @@ PEAK_FP32_VALU_UNPACKED = 78.6e12  # 256 CU x 4 SIMD x 16 lanes x 2 x 2.4 GHz wi
 # for the kernel sources they were taken on.
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "me_kernel_gg_ttgg_1e6_traffic.json")
 KERNEL_SOURCES = ["me_kernel.h", "kernels.h", "helas.h", "card.h", "check.h", "colour_mfma.h", "proc_gg_ttgg.hip",
+                  "lightcone.h", "ordered.h", "ordered_kernel.h", "card_source.h", "ordered_gg_ttgg.hip",
                   "generated/gen_gg_ttgg.h"]
+# FLOP that the double-precision kernels execute per |M|^2 (they share currents
+# between diagrams and helicities, or evaluate two weights per event): the
+# SQ_INSTS_VALU_{ADD,MUL,FMA}_F64 counters times 64 lanes, an FMA as two
+# (profiles/double_precision_kernels.md).
+FP64_FLOPS = {"gg_ttgg": 302_832, "gg_tttt": 227_400, "uu_eeg": 445, "ee_mumu": 218}
 
 
 def kernel_sources_hash():
@@ -179,8 +184,8 @@ def workload_leg(rw, torch, proc, orig, new, n, steps, warmup, oracle_sample):
         dt = (time.perf_counter() - t0) / steps
         guard = rw.rwgt_mixed_guard_count(r.ctx)
         r.me2(p_dev, orig.row(proc), me)
-        flops = rw.rwgt_flops(r.ctx) * n * 2
-        flops_exec = rw.rwgt_flops_executed(r.ctx) * n * 2
+        plain = rw.rwgt_flops(r.ctx) * n * 2
+        flops = (FP64_FLOPS[proc] if mode == "fp64" else rw.rwgt_flops_executed(r.ctx)) * n * 2
         r.close()
         wh, meh = w.cpu().numpy()[0], me.cpu().numpy()[0]
         out[mode] = wh
@@ -190,7 +195,7 @@ def workload_leg(rw, torch, proc, orig, new, n, steps, warmup, oracle_sample):
                       "me2_max_rel_err_vs_oracle": float(np.max(np.abs(meh[idx] / ref_me - 1.0))),
                       "roofline": {"bound": "alu", "achieved": flops / (kernel_ms * 1e-3) / 1e12, "peak": 78.6,
                                    "unit": "TFLOP/s", "frac": flops / (kernel_ms * 1e-3) / PEAK_FP64_VALU,
-                                   "executed_frac": flops_exec / (kernel_ms * 1e-3) / PEAK_FP64_VALU}}
+                                   "plain_sum_rate": plain / (kernel_ms * 1e-3) / 1e12}}
         if mode == "mixed":
             rel = np.abs(wh / out["fp64"] - 1.0)
             legs[mode].update({"w_max_rel_err_vs_fp64_path": float(rel.max()),
@@ -436,20 +441,21 @@ def main():
     nsets = rows.shape[0]
 
     def roofline(r, peak, mode):
-        # algorithmic: the plain per-helicity sum over all 64 kept helicities;
-        # executed: the 32 the kernel evaluates (|M_h|^2 = |M_~h|^2 in QCD)
-        flops = r["flops_per_me2"] * a.events * (1 + nsets)
-        flops_exec = r["flops_exec_per_me2"] * a.events * (1 + nsets)
+        # achieved: the FLOP the kernel executes; plain_sum_rate: those of the
+        # plain sum of every diagram over all 64 kept helicities, in its place
+        evals = a.events * (1 + nsets)
+        flops = (FP64_FLOPS["gg_ttgg"] if mode == "fp64" else r["flops_exec_per_me2"]) * evals
+        plain = r["flops_per_me2"] * evals
         ach = flops / (r["me_ms"] * 1e-3)
-        ach_exec = flops_exec / (r["me_ms"] * 1e-3)
         return {"bound": "alu", "achieved": ach / 1e12, "peak": peak / 1e12, "unit": "TFLOP/s",
                 "frac": ach / peak, "traffic": measured_traffic(mode, a.events),
-                "kernel": "me_kernel<Proc_gg_ttgg>", "flops_per_launch": flops,
-                "executed_flops_per_launch": flops_exec, "executed_achieved": ach_exec / 1e12,
-                "executed_frac": ach_exec / peak,
-                "flops_definition": "achieved/frac: the plain per-helicity sum over all 64 helicities (rwgt_flops); "
-                                    "executed_*: the 32 the kernel evaluates, one of each pair with every helicity "
-                                    "reversed, whose |M_h|^2 are equal in QCD (rwgt_flops_executed)"}
+                "kernel": "ordered_kernel<Proc_gg_ttgg>" if mode == "fp64" else "me_kernel<Proc_gg_ttgg>",
+                "flops_per_launch": flops, "plain_sum_flops": plain,
+                "plain_sum_rate": plain / (r["me_ms"] * 1e-3) / 1e12,
+                "flops_definition": "achieved/frac: what the kernel executes (FP64: the colour-ordered recursion, from "
+                                    "counters; mixed: every diagram for the 32 evaluated helicities, "
+                                    "rwgt_flops_executed); plain_sum_*: every diagram for all 64 helicities "
+                                    "(rwgt_flops), the work a direct evaluation would take"}
 
     main_mode = "fp64" if "fp64" in res else next(iter(res))
     m = res[main_mode]
