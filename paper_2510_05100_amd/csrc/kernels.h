@@ -55,14 +55,18 @@ size_t fp64_table(int proc, const CardPair* cards, int n, void* out);
 // w_out is non-null, card 0 is the original card and
 // w_out[k-1][i] = (w_in[i] * (1/|M|^2_0)) * |M|^2_k for k >= 1.
 // soa: [npart * 4][nevt].
+// parts: me_parts_bytes of workspace where that is not 0 (else null).
 hipError_t launch_me(int proc, int precision, const double* soa, int64_t nevt, const CardPair* cards, int ncards,
-                     const double* w_in, double* w_out, double* me_out, hipStream_t s);
+                     const double* w_in, double* w_out, double* me_out, void* parts, hipStream_t s);
 
 // Default threshold of the mixed path's cancellation guard: measured on 4e6
 // g g -> t t~ g g events (FP16 colour sum), it re-evaluates 0.10 % of them and
 // leaves a largest w' error of 3.6e-6 (none: 6.9e-6); on 1e6 u u~ -> e+ e- g
 // events 0.13 % and 2.3e-6 on w', 4.1e-6 on |M|^2 (none: 6.0e-5).
 constexpr double kGuardKappaDefault = 300.0;
+
+// Workspace of the mixed path's form with a wave per helicity (me_kernel.h).
+constexpr int64_t kPartBytes = 512 << 20;
 
 // Cancellation guard of the mixed path (me_kernel.h, launch_me_guarded).
 struct GuardArgs {
@@ -77,7 +81,8 @@ struct GuardArgs {
 // soa: [npart * 4][nevt], mom: the same momenta as [nevt][npart][4].
 hipError_t launch_me_guarded(int proc, int precision, const double* soa, const double* mom, int64_t nevt, const CardPair* cards,
                              int ncards, const double* w_in, double* w_out, double* me_out, const GuardArgs& g,
-                             hipStream_t s);
+                             void* parts, hipStream_t s);
+size_t me_parts_bytes(int proc, int64_t nevt, int ncards);
 
 // Reweighted cross sections and errors per card: out[k] = {sigma', dsigma', fallback flag};
 // at most nblocks workgroups per card, xsec_blocks of them: part must hold
@@ -119,10 +124,13 @@ double process_flops(int proc, bool executed);
   hipError_t launch_fp64_##NAME(const Fp64Call& a, hipStream_t s);                                       \
   size_t fp64_table_##NAME(const CardPair* cards, int n, void* out);                                     \
   hipError_t launch_me_##NAME(int precision, const double* soa, int64_t nevt, const CardPair* cards,     \
-                              int ncards, const double* w_in, double* w_out, double* me_out, hipStream_t s); \
+                              int ncards, const double* w_in, double* w_out, double* me_out, void* parts,    \
+                              hipStream_t s);                                                            \
+  size_t me_parts_##NAME(int64_t nevt, int ncards);                                                     \
   hipError_t launch_me_guarded_##NAME(int precision, const double* soa, const double* mom, int64_t nevt,  \
                                       const CardPair* cards, int ncards, const double* w_in,             \
-                                      double* w_out, double* me_out, const GuardArgs& g, hipStream_t s);  \
+                                      double* w_out, double* me_out, const GuardArgs& g, void* parts,     \
+                                      hipStream_t s);                                                    \
   void constants_##NAME(int* npart, int* ngood, int* ncol, int* ndiag);                                 \
   double flops_##NAME(bool executed);
 RWGT_DECLARE_PROCESS(ee_mumu)

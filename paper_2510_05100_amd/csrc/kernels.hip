@@ -330,30 +330,40 @@ size_t fp64_table(int proc, const CardPair* cards, int n, void* out) {
 }
 
 hipError_t launch_me(int proc, int precision, const double* soa, int64_t nevt, const CardPair* cards, int ncards,
-                     const double* w_in, double* w_out, double* me_out, hipStream_t s) {
+                     const double* w_in, double* w_out, double* me_out, void* parts, hipStream_t s) {
   switch (proc) {
-    case kProcEeMumu: return launch_me_ee_mumu(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, s);
-    case kProcUuEeg: return launch_me_uu_eeg(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, s);
-    case kProcGgTtgg: return launch_me_gg_ttgg(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, s);
-    case kProcGgTttt: return launch_me_gg_tttt(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, s);
+    case kProcEeMumu: return launch_me_ee_mumu(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, parts, s);
+    case kProcUuEeg: return launch_me_uu_eeg(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, parts, s);
+    case kProcGgTtgg: return launch_me_gg_ttgg(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, parts, s);
+    case kProcGgTttt: return launch_me_gg_tttt(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, parts, s);
   }
   return hipErrorInvalidValue;
 }
 
 hipError_t launch_me_guarded(int proc, int precision, const double* soa, const double* mom, int64_t nevt,
                              const CardPair* cards, int ncards, const double* w_in, double* w_out, double* me_out, const GuardArgs& g,
-                             hipStream_t s) {
+                             void* parts, hipStream_t s) {
   switch (proc) {
     case kProcEeMumu:
-      return launch_me_guarded_ee_mumu(precision, soa, mom, nevt, cards, ncards, w_in, w_out, me_out, g, s);
+      return launch_me_guarded_ee_mumu(precision, soa, mom, nevt, cards, ncards, w_in, w_out, me_out, g, parts, s);
     case kProcUuEeg:
-      return launch_me_guarded_uu_eeg(precision, soa, mom, nevt, cards, ncards, w_in, w_out, me_out, g, s);
+      return launch_me_guarded_uu_eeg(precision, soa, mom, nevt, cards, ncards, w_in, w_out, me_out, g, parts, s);
     case kProcGgTtgg:
-      return launch_me_guarded_gg_ttgg(precision, soa, mom, nevt, cards, ncards, w_in, w_out, me_out, g, s);
+      return launch_me_guarded_gg_ttgg(precision, soa, mom, nevt, cards, ncards, w_in, w_out, me_out, g, parts, s);
     case kProcGgTttt:
-      return launch_me_guarded_gg_tttt(precision, soa, mom, nevt, cards, ncards, w_in, w_out, me_out, g, s);
+      return launch_me_guarded_gg_tttt(precision, soa, mom, nevt, cards, ncards, w_in, w_out, me_out, g, parts, s);
   }
   return hipErrorInvalidValue;
+}
+
+size_t me_parts_bytes(int proc, int64_t nevt, int ncards) {
+  switch (proc) {
+    case kProcEeMumu: return me_parts_ee_mumu(nevt, ncards);
+    case kProcUuEeg: return me_parts_uu_eeg(nevt, ncards);
+    case kProcGgTtgg: return me_parts_gg_ttgg(nevt, ncards);
+    case kProcGgTttt: return me_parts_gg_tttt(nevt, ncards);
+  }
+  return 0;
 }
 
 void process_constants(int proc, int* npart, int* ngood, int* ncol, int* ndiag) {

@@ -212,10 +212,140 @@ __global__ __launch_bounds__(kMeBlock) void me_kernel(const double* __restrict__
 
 static __global__ void zero_count_kernel(unsigned int* c) { *c = 0u; }
 
+// The same with a wave per 64 events and helicity, for launches that one wave
+// per half of the helicities leaves unbalanced: at one wave per SIMD 1e5
+// g g -> t t~ g g events are 3.05 rounds of 16 helicities, the last nearly
+// empty, and 777 events are 26 of 1024 SIMDs.  A wave writes what its helicity
+// adds under each card (and, for few waves, a wave per card too); the join
+// below adds the helicities up as me_kernel does, so the results are the same
+// to the bit.  g g -> t t~ g g, one new card: 777 events 1.57 -> 0.10 ms, 20,011
+// 1.73 -> 1.09, 1e5 6.3 -> 5.0, 2e5 11.0 -> 9.9 (1e6 events: 48 ms, nothing to
+// gain); u u~ -> e+ e- g, 77,777 events, 3 new cards: 0.27 -> 0.14 ms.
+struct MePart { double me; float inco, coh; };    // of one helicity, card and event; all three as evaluated
+constexpr int kPartWaves = 4;                     // per workgroup
+template <class PROC, class R, class CT, bool GUARD>
+__global__ __launch_bounds__(64 * kPartWaves) void me_part_kernel(const double* __restrict__ soa, int64_t nevt,
+                                                                  const CardPair* __restrict__ cards, int ncards,
+                                                                  int nper, MePart* __restrict__ parts) {
+  constexpr bool kMfma = !std::is_void<CT>::value;
+  static_assert(sizeof(R) == 4, "the parts hold single-precision sums");
+  static_assert(PROC::NSUM % kPartWaves == 0, "whole workgroups");
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+  const int ih0 = (int(blockIdx.y) * kPartWaves + wave) * nper;   // wave-uniform
+  const int64_t r = int64_t(blockIdx.x) * 64 + (threadIdx.x & 63);
+  const bool valid = r < nevt;                                // lanes past the end: the last event (see me_kernel)
+  const int64_t i = valid ? r : nevt - 1;
+  double P[PROC::NPART][4];
+#pragma unroll
+  for (int a = 0; a < PROC::NPART; ++a)
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) P[a][mu] = RWGT_AT(soa, int64_t(a * 4 + mu) * nevt + i, PROC::NPART * 4 * nevt);
+  [[maybe_unused]] __shared__ typename ColourLdsOf<CT>::type lds_colour[kMfma ? kPartWaves : 1];
+  [[maybe_unused]] std::conditional_t<kMfma, ColourMfma<PROC::NCOL, std::conditional_t<kMfma, CT, _Float16>>, char> cm;
+  if constexpr (kMfma) cm.init(PROC::cnum(), lds_colour[wave]);
+  for (int k = int(blockIdx.z); k < ncards; k += int(gridDim.z)) {
+    const Card<R>& cd = pick<R>(RWGT_AT(cards, k, ncards));
+    MePart out = {0.0, 0.0f, 0.0f};
+    // one trip, as a loop of sums: without it the compiler spills 140 registers
+    // (the loop's end keeps what the store needs out of the amplitude code)
+    for (int ih = ih0; ih < ih0 + nper; ++ih) {
+      std::conditional_t<GUARD, GuardJamp<R, PROC::NCOL>, cx<R>[PROC::NCOL]> jamp;
+      PROC::template jamps<R>(P, PROC::good(ih), cd, jamp);
+      if constexpr (kMfma) {
+        out.me += cm.sum(flows(jamp), lds_colour[wave]);
+      } else {
+        out.me += double(PROC::template colour_sum<R>(jamp));
+      }
+      if constexpr (GUARD) {
+        R c2 = R(0);
+#pragma unroll
+        for (int c = 0; c < PROC::NCOL; ++c) c2 += jamp[c].re * jamp[c].re + jamp[c].im * jamp[c].im;
+        out.coh += c2;
+        out.inco += jamp.inco;
+      }
+    }
+    if (valid)
+      RWGT_AT(parts, (int64_t(k) * PROC::NSUM + ih0) * nevt + i, int64_t(ncards) * PROC::NSUM * nevt) = out;
+  }
+}
+
+// The parts of each event in me_kernel's order: the helicities of each of its
+// waves in sequence, then the waves.
+template <class PROC, bool MFMA, bool GUARD>
+__global__ __launch_bounds__(256) void me_join_kernel(const MePart* __restrict__ parts, int64_t nevt, int ncards,
+                                                      const double* __restrict__ w_in, double* __restrict__ w_out,
+                                                      double* __restrict__ me_out, const GuardArgs g) {
+  constexpr int HS = hel_split<PROC>(), NH = PROC::NSUM / HS;
+  const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
+  if (i >= nevt) return;
+  double norm = 0.0;
+  [[maybe_unused]] double kappa = 0.0;
+  for (int k = 0; k < ncards; ++k) {
+    double me = 0.0, inco = 0.0, coh = 0.0;
+#pragma unroll
+    for (int w = 0; w < HS; ++w) {
+      double m = 0.0, a = 0.0, c = 0.0;
+#pragma unroll 8
+      for (int h = w * NH; h < (w + 1) * NH; ++h) {
+        const MePart p = RWGT_AT(parts, (int64_t(k) * PROC::NSUM + h) * nevt + i, int64_t(ncards) * PROC::NSUM * nevt);
+        m = MFMA ? __builtin_fma(p.me, 1.0 / PROC::CDEN, m) : m + p.me;
+        a += double(p.inco);
+        c += double(p.coh);
+      }
+      me = w ? me + m : m;
+      inco = w ? inco + a : a;
+      coh = w ? coh + c : c;
+    }
+    if constexpr (GUARD) {
+      const double kk = coh > 0.0 ? inco / coh : (inco > 0.0 ? __builtin_inf() : 0.0);
+      kappa = kk > kappa || !(kk == kk) ? kk : kappa;
+    }
+    me *= PROC::SCALE;
+    if (me_out) RWGT_AT(me_out, int64_t(k) * nevt + i, int64_t(ncards) * nevt) = me;
+    if (w_out) {
+      if (k == 0) {
+        norm = (me == 0.0 ? 0.0 : 1.0 / me) * RWGT_AT(w_in, i, nevt);
+      } else {
+        RWGT_AT(w_out, int64_t(k - 1) * nevt + i, int64_t(ncards - 1) * nevt) = norm * me;
+      }
+    }
+  }
+  if constexpr (GUARD) {
+    if (g.kappa) RWGT_AT(g.kappa, i, nevt) = kappa;
+    if (g.flagged && !(kappa <= g.kmax)) RWGT_AT(g.flagged, atomicAdd(g.nflagged, 1u), nevt) = int32_t(i);
+  }
+}
+
+// Bytes of the parts, 0: me_kernel itself.  Many-flow kernels hold a SIMD each:
+// from 10 rounds of me_kernel's waves on, the last one costs under 5 %.
+// Few-flow kernels fit several waves on a SIMD and fill the chip at 4096; the
+// join is one launch more (6 us), which fewer than 16 amplitudes in sequence do
+// not repay (e+ e- -> mu+ mu- under two cards has 8: 51 us as it is, 57 split;
+// u u~ -> e+ e- g has 16: 84 and 53).
+template <class PROC>
+inline size_t me_parts_t(int64_t nevt, int ncards) {
+  constexpr bool many = hel_split<PROC>() > 1;
+  const int64_t waves = (nevt + 63) / 64 * hel_split<PROC>();
+  if (waves > (many ? 10240 : 4096) || (!many && int64_t(PROC::NSUM) * ncards < 16)) return 0;
+  const int64_t each = int64_t(sizeof(MePart)) * PROC::NSUM * nevt;
+  return ncards <= kPartBytes / each ? size_t(each * ncards) : 0;
+}
+
 template <class PROC, class R, class CT, bool GUARD = false>
 inline hipError_t launch_me_t(const double* soa, int64_t nevt, const CardPair* cards, int ncards,
-                              const double* w_in, double* w_out, double* me_out, hipStream_t s,
+                              const double* w_in, double* w_out, double* me_out, void* parts, hipStream_t s,
                               const GuardArgs& g = GuardArgs{}) {
+  if (parts) {
+    const int64_t groups = (nevt + 63) / 64;
+    const bool by_card = groups * PROC::NSUM < 2048 && ncards <= 65535;   // two waves per SIMD
+    hipLaunchKernelGGL((me_part_kernel<PROC, R, CT, GUARD>),
+                       dim3(unsigned(groups), unsigned(PROC::NSUM / kPartWaves), unsigned(by_card ? ncards : 1)),
+                       dim3(64 * kPartWaves), 0, s, soa,
+                       nevt, cards, ncards, 1, static_cast<MePart*>(parts));
+    hipLaunchKernelGGL((me_join_kernel<PROC, !std::is_void<CT>::value, GUARD>), dim3(unsigned((nevt + 255) / 256)),
+                       dim3(256), 0, s, static_cast<const MePart*>(parts), nevt, ncards, w_in, w_out, me_out, g);
+    return hipGetLastError();
+  }
   constexpr int B = me_block<PROC>(), EPB = hel_split<PROC>() > 1 ? 64 : B;
   const int64_t blocks = (nevt + EPB - 1) / EPB;
   hipLaunchKernelGGL((me_kernel<PROC, R, CT, GUARD>), dim3(unsigned(blocks)), dim3(B), 0, s, soa, nevt,
@@ -227,14 +357,15 @@ inline hipError_t launch_me_t(const double* soa, int64_t nevt, const CardPair* c
 // flags the events whose kappa exceeds g.kmax (g.kmax < 0: none, kappa only).
 template <class PROC>
 inline hipError_t launch_me_flag_t(int precision, const double* soa, int64_t nevt, const CardPair* cards, int ncards,
-                                   const double* w_in, double* w_out, double* me_out, GuardArgs g, hipStream_t s) {
+                                   const double* w_in, double* w_out, double* me_out, GuardArgs g, void* parts,
+                                   hipStream_t s) {
   constexpr bool many = PROC::NCOL >= 8;
   if (g.nflagged) hipLaunchKernelGGL(zero_count_kernel, dim3(1), dim3(1), 0, s, g.nflagged);
   return precision == kPrecMixedBF16
       ? launch_me_t<PROC, float, std::conditional_t<many, __bf16, void>, true>(soa, nevt, cards, ncards, w_in, w_out,
-                                                                               me_out, s, g)
+                                                                               me_out, parts, s, g)
       : launch_me_t<PROC, float, std::conditional_t<many, _Float16, void>, true>(soa, nevt, cards, ncards, w_in,
-                                                                                 w_out, me_out, s, g);
+                                                                                 w_out, me_out, parts, s, g);
 }
 inline bool reevaluates(const GuardArgs& g) { return !(g.kmax < 0.0) && g.flagged && g.nflagged; }
 
@@ -242,13 +373,13 @@ inline bool reevaluates(const GuardArgs& g) { return !(g.kmax < 0.0) && g.flagge
 // (FP16 or BF16 split) for many-flow processes, on the VALU otherwise.
 template <class PROC>
 inline hipError_t launch_me_prec(int precision, const double* soa, int64_t nevt, const CardPair* cards, int ncards,
-                                 const double* w_in, double* w_out, double* me_out, hipStream_t s) {
+                                 const double* w_in, double* w_out, double* me_out, void* parts, hipStream_t s) {
   constexpr bool many = PROC::NCOL >= 8;
   if (precision == kPrecMixedBF16)
     return launch_me_t<PROC, float, std::conditional_t<many, __bf16, void>>(soa, nevt, cards, ncards, w_in, w_out,
-                                                                             me_out, s);
+                                                                             me_out, parts, s);
   return launch_me_t<PROC, float, std::conditional_t<many, _Float16, void>>(soa, nevt, cards, ncards, w_in, w_out,
-                                                                             me_out, s);
+                                                                             me_out, parts, s);
 }
 
 }  // namespace rwgt

@@ -16,14 +16,16 @@ size_t fp64_table_ee_mumu(const CardPair* cards, int n, void* out) {
 }
 
 hipError_t launch_me_ee_mumu(int precision, const double* soa, int64_t nevt, const CardPair* cards, int ncards,
-                         const double* w_in, double* w_out, double* me_out, hipStream_t s) {
-  return launch_me_prec<Proc_ee_mumu>(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, s);
+                         const double* w_in, double* w_out, double* me_out, void* parts, hipStream_t s) {
+  return launch_me_prec<Proc_ee_mumu>(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, parts, s);
 }
+size_t me_parts_ee_mumu(int64_t nevt, int ncards) { return me_parts_t<Proc_ee_mumu>(nevt, ncards); }
 
 hipError_t launch_me_guarded_ee_mumu(int precision, const double* soa, const double* mom, int64_t nevt,
                                     const CardPair* cards, int ncards, const double* w_in, double* w_out, double* me_out,
-                                    const GuardArgs& g, hipStream_t s) {
-  const hipError_t e = launch_me_flag_t<Proc_ee_mumu>(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, g, s);
+                                    const GuardArgs& g, void* parts, hipStream_t s) {
+  const hipError_t e = launch_me_flag_t<Proc_ee_mumu>(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, g,
+                                                      parts, s);
   if (e != hipSuccess || !reevaluates(g)) return e;
   return ew::launch_rows<4>(mom, nevt, cards, ncards, gen_ee_mumu::AVERAGE, w_in, w_out, me_out, g.flagged, g.nflagged,
                             s);

@@ -11,14 +11,16 @@ hipError_t launch_fp64_gg_tttt(const Fp64Call& a, hipStream_t s) { return launch
 size_t fp64_table_gg_tttt(const CardPair* cards, int n, void* out) { return qcd_table(cards, n, out); }
 
 hipError_t launch_me_gg_tttt(int precision, const double* soa, int64_t nevt, const CardPair* cards, int ncards,
-                         const double* w_in, double* w_out, double* me_out, hipStream_t s) {
-  return launch_me_prec<Proc_gg_tttt>(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, s);
+                         const double* w_in, double* w_out, double* me_out, void* parts, hipStream_t s) {
+  return launch_me_prec<Proc_gg_tttt>(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, parts, s);
 }
+size_t me_parts_gg_tttt(int64_t nevt, int ncards) { return me_parts_t<Proc_gg_tttt>(nevt, ncards); }
 
 hipError_t launch_me_guarded_gg_tttt(int precision, const double* soa, const double* mom, int64_t nevt,
                                     const CardPair* cards, int ncards, const double* w_in, double* w_out, double* me_out,
-                                    const GuardArgs& g, hipStream_t s) {
-  const hipError_t e = launch_me_flag_t<Proc_gg_tttt>(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, g, s);
+                                    const GuardArgs& g, void* parts, hipStream_t s) {
+  const hipError_t e = launch_me_flag_t<Proc_gg_tttt>(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, g,
+                                                      parts, s);
   if (e != hipSuccess || !reevaluates(g)) return e;
   return launch_ordered_rows_gg_tttt(mom, nevt, cards, ncards, w_in, w_out, me_out, g.flagged, g.nflagged, s);
 }

@@ -16,14 +16,16 @@ size_t fp64_table_uu_eeg(const CardPair* cards, int n, void* out) {
 }
 
 hipError_t launch_me_uu_eeg(int precision, const double* soa, int64_t nevt, const CardPair* cards, int ncards,
-                         const double* w_in, double* w_out, double* me_out, hipStream_t s) {
-  return launch_me_prec<Proc_uu_eeg>(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, s);
+                         const double* w_in, double* w_out, double* me_out, void* parts, hipStream_t s) {
+  return launch_me_prec<Proc_uu_eeg>(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, parts, s);
 }
+size_t me_parts_uu_eeg(int64_t nevt, int ncards) { return me_parts_t<Proc_uu_eeg>(nevt, ncards); }
 
 hipError_t launch_me_guarded_uu_eeg(int precision, const double* soa, const double* mom, int64_t nevt,
                                    const CardPair* cards, int ncards, const double* w_in, double* w_out, double* me_out,
-                                    const GuardArgs& g, hipStream_t s) {
-  const hipError_t e = launch_me_flag_t<Proc_uu_eeg>(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, g, s);
+                                    const GuardArgs& g, void* parts, hipStream_t s) {
+  const hipError_t e = launch_me_flag_t<Proc_uu_eeg>(precision, soa, nevt, cards, ncards, w_in, w_out, me_out, g,
+                                                      parts, s);
   if (e != hipSuccess || !reevaluates(g)) return e;
   return ew::launch_rows<5>(mom, nevt, cards, ncards, gen_uu_eeg::AVERAGE, w_in, w_out, me_out, g.flagged, g.nflagged,
                             s);

@@ -161,6 +161,8 @@ struct rwgt_ctx {
   CardPair* dcards = nullptr;
   int dcards_cap = 0;
   CardPair* hcards = nullptr;   // pinned staging for the card upload
+  void* me_parts = nullptr;     // mixed: what each helicity adds (me_kernel.h)
+  size_t me_parts_cap = 0;
   int hcards_cap = 0;
   hipEvent_t upload_done = nullptr;
   bool upload_pending = false;
@@ -225,7 +227,7 @@ struct rwgt_ctx {
                     static_cast<void*>(sur_cards), static_cast<void*>(sur_cpar), static_cast<void*>(fac_probe),
                     static_cast<void*>(fac_cards), static_cast<void*>(as_cards), static_cast<void*>(nf_part),
                     static_cast<void*>(guard_list), static_cast<void*>(guard_count), static_cast<void*>(stage),
-                    static_cast<void*>(xsec_part)})
+                    static_cast<void*>(xsec_part), me_parts})
       if (p) hipFree(p);
     if (xsec_host) hipHostFree(xsec_host);
     if (nf_host) hipHostFree(nf_host);
@@ -295,6 +297,22 @@ int ensure_guard(rwgt_ctx* c, int64_t nevt) {
   if (e == hipSuccess) e = hipMalloc(&c->guard_list, size_t(nevt) * sizeof(int32_t));
   if (e != hipSuccess) return c->hip_fail(e, "hipMalloc(guard list)");
   c->guard_cap = nevt;
+  return RWGT_OK;
+}
+
+// Workspace of the mixed path's wave-per-helicity form (null: not used).
+int ensure_parts(rwgt_ctx* c, int64_t nevt, int ncards, void*& parts) {
+  parts = nullptr;
+  const size_t bytes = rwgt::me_parts_bytes(c->def->id, nevt, ncards);
+  if (bytes == 0) return RWGT_OK;
+  if (bytes > c->me_parts_cap) {
+    if (c->me_parts) { hipStreamSynchronize(c->stream); hipFree(c->me_parts); c->me_parts = nullptr; }
+    c->me_parts_cap = 0;
+    const hipError_t e = hipMalloc(&c->me_parts, bytes);
+    if (e != hipSuccess) return c->hip_fail(e, "hipMalloc(helicity parts)");
+    c->me_parts_cap = bytes;
+  }
+  parts = c->me_parts;
   return RWGT_OK;
 }
 
@@ -379,7 +397,9 @@ int run(rwgt_ctx* c, bool reweight, const double* momenta, int64_t nevt, const d
     }
     return run_fp64(c, a, cards);
   }
+  void* parts = nullptr;
   rc = ensure_buffers(c, nevt, int(cards.size()));
+  if (rc == RWGT_OK) rc = ensure_parts(c, nevt, int(cards.size()), parts);
   if (rc == RWGT_OK) rc = cards_ready(c);
   if (rc != RWGT_OK) return rc;
   std::memcpy(c->hcards, cards.data(), cards.size() * sizeof(CardPair));
@@ -403,10 +423,10 @@ int run(rwgt_ctx* c, bool reweight, const double* momenta, int64_t nevt, const d
       c->guard_ran = true;
     }
     e = rwgt::launch_me_guarded(c->def->id, c->precision, c->soa, momenta, nevt, c->dcards, int(cards.size()), w_in,
-                                w_out, me_out, g, c->stream);
+                                w_out, me_out, g, parts, c->stream);
   } else {
     e = rwgt::launch_me(c->def->id, c->precision, c->soa, nevt, c->dcards, int(cards.size()), w_in, w_out, me_out,
-                        c->stream);
+                        parts, c->stream);
   }
   if (e != hipSuccess) return c->hip_fail(e, "matrix-element kernel");
   if (c->profiling) hipEventRecord(c->ev[2], c->stream);
@@ -727,8 +747,10 @@ int rwgt_eval_factored(rwgt_ctx* c, const double* momenta, int64_t nevt, const d
       if (e != hipSuccess) return c->hip_fail(e, "hipMalloc(factor cards)");
       c->fac_cards_cap = int(fc.size());
     }
+    void* parts = nullptr;
     if (!fp64) {
-      rc = cards_ready(c);
+      rc = ensure_parts(c, nevt, nprobe, parts);
+      if (rc == RWGT_OK) rc = cards_ready(c);
       if (rc != RWGT_OK) return rc;
       std::memcpy(c->hcards, probes.data(), probes.size() * sizeof(CardPair));
       rc = upload_cards(c, probes.size() * sizeof(CardPair));
@@ -751,7 +773,7 @@ int rwgt_eval_factored(rwgt_ctx* c, const double* momenta, int64_t nevt, const d
       e = rwgt::launch_ingest(c->def->npart, momenta, c->soa, nevt, c->stream);
       if (e == hipSuccess)
         e = rwgt::launch_me(id, c->precision, c->soa, nevt, c->dcards, nprobe, nullptr, nullptr, c->fac_probe,
-                            c->stream);
+                            parts, c->stream);
     }
     if (e == hipSuccess)
       e = rwgt::launch_factored(ew, c->soa, c->def->npart, nevt, ia, ib, c->fac_probe, o.mz, o.wz, c->fac_cards,
