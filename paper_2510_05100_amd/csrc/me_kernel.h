@@ -35,6 +35,10 @@ namespace rwgt {
     static __device__ __forceinline__ R colour_sum(const J& j) {                               \
       return gen_##NAME::colour_sum<R>(j);                                                     \
     }                                                                                          \
+    template <class R, class J>                                                                \
+    static __device__ __forceinline__ R colour_sum_paired(J& j) {                              \
+      return gen_##NAME::colour_sum_paired<R>(j);                                              \
+    }                                                                                          \
   };
 
 template <class R> __device__ __forceinline__ const Card<R>& pick(const CardPair& c);

@@ -113,18 +113,20 @@ struct QuarkPairs {                              // g g -> Q Q~ Q Q~
 // list; otherwise all nevt events, one workgroup per pair.
 //
 // Bound by the vector ALUs: they issue in 89 % of the cycles, 85 % of it FP64.
-// A wave evaluates a card of its two events in 6300 vector instructions, where
+// A wave evaluates a card of its two events in 5850 vector instructions, where
 // evaluating every diagram for every helicity takes about 5 times that
-// (g g -> t t~ g g; g g -> t t~ t t~ 4 times).  Two waves per SIMD (LDS 17 KB
+// (g g -> t t~ g g; g g -> t t~ t t~ 4 times); the colour sum is 260 of them,
+// 650 without the flows' sums and differences.  Two waves per SIMD (LDS 17 KB
 // per wave, 256 registers, 28 spilled; 166, none) hide the LDS latency; the
 // fences (load_fence, settle) hold the compiler to the order of the source,
 // without them it loads everything first and spills 1000 registers.  1e6
-// events, one new card: 12.5 - 14.4 ms (from card to card; 75 ms diagram by
-// diagram, one lane per event and two waves splitting its helicities), 777
-// events: 0.035 (2.4) ms; g g -> t t~ t t~, 250001 events: 2.48 (9.32) ms.  A
-// first form for g g -> t t~ g g with two waves per 64
-// events and one lane per event shared the gluon currents only and needed 512
-// registers with 310 spilled, waiting in half of its cycles: 29.7 ms.
+// events, one new card: 11.9 ms (75 ms diagram by diagram, one lane per event
+// and two waves splitting its helicities; 12.9 with the plain colour sum, which
+// other cards of the type ran in 12.5 to 14.4 as their clock allows), 777
+// events: 0.034 (2.4) ms; g g -> t t~ t t~, 250001 events: 2.45 (9.36) ms.  A
+// first form for g g -> t t~ g g with two waves per 64 events and one lane per
+// event shared the gluon currents only and needed 512 registers with 310
+// spilled, waiting in half of its cycles: 29.7 ms.
 template <class PROC, class REC, bool LISTED, class CARDS>
 __global__ __launch_bounds__(64, 2) void ordered_kernel(const double* __restrict__ mom, int64_t nevt,
                                                         const CARDS cards, int ncards,
@@ -150,8 +152,8 @@ __global__ __launch_bounds__(64, 2) void ordered_kernel(const double* __restrict
     for (int k = 0; k < ncards; ++k) {
       const auto& cd = cards(k);                 // read where it is used: held, it would cost registers
       wave_sync();
-      double me = REC::lane(m, opq_index(t), mom, nevt, i, cd, [](const cx<double>(&f)[PROC::NCOL]) {
-        return PROC::template colour_sum<double>(f);
+      double me = REC::lane(m, opq_index(t), mom, nevt, i, cd, [](cx<double>(&f)[PROC::NCOL]) {
+        return PROC::template colour_sum_paired<double>(f);
       });
 #pragma unroll
       for (int d = 1; d < kLanes; d <<= 1) me += __shfl_xor(me, d);

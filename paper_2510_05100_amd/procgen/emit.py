@@ -23,6 +23,7 @@ such processes GOOD lists one helicity of each reversed pair first (particle
 """
 from __future__ import annotations
 
+import itertools
 import math
 from fractions import Fraction
 from typing import Dict, List
@@ -318,6 +319,87 @@ def colour_matrix_ints(d: Diagrams):
         for j, x in enumerate(row):
             assert Fraction(num[i][j], den) == x
     return num, den
+
+
+def flow_involutions(d: Diagrams, num):
+    """Involutions of the colour flows that leave the colour matrix as it is: relabelled gluons, reversed
+    strings and (two lines) exchanged strings and exchanged columns."""
+    index = {b: i for i, b in enumerate(d.basis)}
+    found = []
+
+    def keep(image):
+        f = [index.get(image(b), -1) for b in d.basis]
+        n = len(f)
+        if (sorted(f) == list(range(n)) and f != list(range(n)) and all(f[f[i]] == i for i in range(n))
+                and all(num[f[i]][f[j]] == num[i][j] for i in range(n) for j in range(n)) and f not in found):
+            found.append(f)
+
+    two = d.term_lines is not None
+    ids = sorted(d.basis[0][1] + d.basis[0][2]) if two else sorted(d.basis[0])
+    cols = sorted({b[0] for b in d.basis}) if two else []
+    for perm in itertools.permutations(ids):
+        m = dict(zip(ids, perm))
+        for reverse in (False, True):
+            def string(x):
+                return tuple(m[g] for g in (reversed(x) if reverse else x))
+            if not two:
+                keep(string)
+                continue
+            for exchange, column in itertools.product((False, True), repeat=2):
+                keep(lambda b: ((cols[1 - cols.index(b[0])] if column else b[0],)
+                                + tuple(string(x) for x in (b[2:0:-1] if exchange else b[1:]))))
+    return found
+
+
+def pair_flows(num, involutions):
+    """The quadratic form after sums and differences of the flows that each involution exchanges: the pairs
+    (i, j) in order (i becomes f_i + f_j, j f_i - f_j) and the form's matrix in the new flows, or None where an
+    involution does not map the flows so far onto each other."""
+    n = len(num)
+    form = [[Fraction(v) for v in row] for row in num]
+    flows = [[int(i == j) for j in range(n)] for i in range(n)]
+    pairs = []
+    for f in involutions:
+        seen = set()
+        for i in range(n):
+            if i in seen:
+                continue
+            seen.add(i)
+            image = [0] * n
+            for a, x in enumerate(flows[i]):
+                image[f[a]] = x
+            if image in (flows[i], [-x for x in flows[i]]):
+                continue
+            at = [j for j in range(n) if flows[j] in (image, [-x for x in image])]
+            if len(at) != 1:
+                return None
+            j = at[0]
+            seen.add(j)
+            pairs.append((i, j))
+            flows[i], flows[j] = ([p + q for p, q in zip(flows[i], flows[j])],
+                                  [p - q for p, q in zip(flows[i], flows[j])])
+            for row in form:
+                row[i], row[j] = (row[i] + row[j]) / 2, (row[i] - row[j]) / 2
+            form[i], form[j] = ([(a + b) / 2 for a, b in zip(form[i], form[j])],
+                                [(a - b) / 2 for a, b in zip(form[i], form[j])])
+    return pairs, form
+
+
+def paired_colour_sum(d: Diagrams, num):
+    """Pairs and form of the fewest operations among up to two commuting involutions."""
+    n = len(num)
+    best = None
+    found = flow_involutions(d, num) if n > 1 else []
+    for chosen in itertools.chain([()], ((f,) for f in found), itertools.permutations(found, 2)):
+        if len(chosen) == 2 and any(chosen[0][chosen[1][i]] != chosen[1][chosen[0][i]] for i in range(n)):
+            continue
+        got = pair_flows(num, chosen)
+        if got is None:
+            continue
+        cost = 4 * len(got[0]) + 2 * sum(1 for i in range(n) for j in range(i, n) if got[1][i][j])
+        if best is None or cost < best[0]:
+            best = (cost, *got)
+    return best[1], best[2]
 
 
 def node_deps(em: "Emitter", key):
@@ -618,6 +700,27 @@ def generate(d: Diagrams) -> str:
         out.append(f"    const R zi = {' + '.join(ti)};")
         out.append(f"    me += jamp[{i}].re * zr + jamp[{i}].im * zi; }}")
     out.append(f"  return me * R(1.0 / {den}.0);")
+    out.append("}")
+    # the same after sums and differences of flows that the colour matrix does not tell apart
+    pairs, form = paired_colour_sum(d, num)
+    scale = math.lcm(*(x.denominator for row in form for x in row))
+    out.append("")
+    out.append("// The same from the flows' sums and differences (in place), in which the colour")
+    out.append("// matrix is nearly block diagonal.")
+    out.append("template <class R, class J>")
+    out.append("__host__ __device__ __forceinline__ R colour_sum_paired(J& jamp) {")
+    for i, j in pairs:
+        out.append(f"  {{ const cx<R> t = jamp[{i}] + jamp[{j}]; jamp[{j}] = jamp[{i}] - jamp[{j}]; jamp[{i}] = t; }}")
+    out.append("  R me = R(0);")
+    for i in range(ncol):
+        c = [(j, int(form[i][j] * scale) * (1 if i == j else 2)) for j in range(i, ncol) if form[i][j]]
+        if not c:
+            continue
+        for part in ("re", "im"):
+            out.append(f"  {'{ ' if part == 're' else '  '}const R z{part[0]} = "
+                       + " + ".join(f"R({v}) * jamp[{j}].{part}" for j, v in c) + ";")
+        out.append(f"    me += jamp[{i}].re * zr + jamp[{i}].im * zi; }}")
+    out.append(f"  return me * R(1.0 / {den * scale}.0);")
     out.append("}")
     out.append(f"}}  // namespace gen_{name}")
     out.append("}  // namespace rwgt")

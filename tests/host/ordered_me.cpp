@@ -67,7 +67,7 @@ int main() {
   for (int t = 0; t < 32; ++t)
     lanes.emplace_back([&, t] {
       auto sync = [&] { pthread_barrier_wait(&bar); };
-      auto colour = [](const cx<double>(&f)[gen::NCOL]) { return gen::colour_sum<double>(f); };
+      auto colour = [](cx<double>(&f)[gen::NCOL]) { return gen::colour_sum_paired<double>(f); };
       for (int e = 0; e < n; ++e) {
         const double* p = &P[size_t(e * 24)];
 #ifdef PAIRS
