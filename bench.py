@@ -40,7 +40,7 @@ KERNEL_SOURCES = ["me_kernel.h", "kernels.h", "helas.h", "card.h", "check.h", "c
 # between diagrams and helicities, or evaluate two weights per event): the
 # SQ_INSTS_VALU_{ADD,MUL,FMA}_F64 counters times 64 lanes, an FMA as two
 # (profiles/double_precision_kernels.md).
-FP64_FLOPS = {"gg_ttgg": 302_832, "gg_tttt": 227_400, "uu_eeg": 445, "ee_mumu": 218}
+FP64_FLOPS = {"gg_ttgg": 275_888, "gg_tttt": 223_680, "uu_eeg": 445, "ee_mumu": 218}
 
 
 def kernel_sources_hash():
