@@ -214,12 +214,13 @@ int rwgt_flops(const rwgt_ctx *ctx, double *flops_per_me2);
  * Errors: RWGT_EINVAL (NULL argument), RWGT_EDEVICE (a counter copy failed). */
 int rwgt_bounds_check(int32_t *enabled, uint64_t *misses);
 
-/* The same count for the helicities the kernels actually evaluate.  For the
+/* The same count for the helicities that have to be evaluated.  For the
  * pure-QCD processes (g g > t t~ g g, g g > t t~ t t~) reversing every
  * helicity leaves |M_h|^2 unchanged (parity of QCD), so of the
  * helicity-summed |M|^2 (MadtRex section, Usage) one helicity of each
  * reversed pair is evaluated and counted twice: half of rwgt_flops.
- * Otherwise equal to rwgt_flops.  Gives the executed rate. */
+ * Otherwise equal to rwgt_flops.  The mixed kernels execute this count; the
+ * double-precision ones share currents or weights and execute less. */
 int rwgt_flops_executed(const rwgt_ctx *ctx, double *flops_per_me2);
 
 /* Reweighted cross sections and their errors for nsets cards (teaRex section):

@@ -318,7 +318,9 @@ static hipError_t launch_batch_t(const BatchSeg* segs, int nseg, int64_t ntiles,
 // helicity good(j % NGOOD) under the original card cards[0] (j < NGOOD) or
 // the event's card cards[1 + card_index[e]], and the group's first lane
 // gathers them and adds each card's values in helicity order, the order of
-// the one-lane-per-event kernels, so w' is the same to the bit.  One
+// the one-lane-per-event kernel: w' is the mixed path's to the bit (the
+// double-precision path evaluates two weights per event and agrees to a few
+// ulp).  One
 // helicity and one card per lane keeps the registers to a few waves per
 // SIMD, and a short fallback list still fills the chip.  Events
 // list[0 .. *count) (the count stays on the device, at most n_all), or
