@@ -110,7 +110,9 @@ struct QuarkPairs {                              // g g -> Q Q~ Q Q~
 
 // Half a wave per event, one lane per evaluated helicity, under every card in
 // turn.  LISTED: the events rows[0 .. *nrows), workgroups striding over the
-// list; otherwise all nevt events, one workgroup per pair.
+// list; otherwise the events from first0 on, one workgroup per pair (no loop
+// around the recursion: the listed form spills 46 registers where this one
+// spills 28).
 //
 // Bound by the vector ALUs: they issue in 89 % of the cycles, 85 % of it FP64.
 // A wave evaluates a card of its two events in 5850 vector instructions, where
@@ -133,12 +135,12 @@ __global__ __launch_bounds__(64, 2) void ordered_kernel(const double* __restrict
                                                         const double* __restrict__ w_in, double* __restrict__ w_out,
                                                         double* __restrict__ me_out, const int32_t* __restrict__ rows,
                                                         const unsigned int* __restrict__ nrows,
-                                                        unsigned long long* __restrict__ nonfinite) {
+                                                        unsigned long long* __restrict__ nonfinite, int64_t first0) {
   __shared__ typename REC::Memory::Event mem[2];
   const int t = int(threadIdx.x) & (kLanes - 1), half = int(threadIdx.x) / kLanes;
   typename REC::Memory m{&mem[half]};
   const int64_t n = LISTED ? int64_t(*nrows) : nevt;
-  int64_t first = int64_t(blockIdx.x) * 2;
+  int64_t first = first0 + int64_t(blockIdx.x) * 2;
   int bad = 0;                                   // non-finite outputs of this half's events
   if (LISTED && first >= n) return;
   do {
@@ -180,20 +182,35 @@ __global__ __launch_bounds__(64, 2) void ordered_kernel(const double* __restrict
   }
 }
 
+// Workgroups of the launch that starts at event first0 of nevt: one per pair of
+// those left, up to 2^25 (2^31 work-items; a launch holds fewer than 2^32, and
+// the pairs of 1.3e8 events, 26 GB of momenta, have as many).
+constexpr int64_t kLaunchGroups = int64_t(1) << 25;
+inline int64_t launch_groups(int64_t nevt, int64_t first0) {
+  const int64_t pairs = (nevt - first0 + 1) / 2;
+  return pairs < kLaunchGroups ? pairs : kLaunchGroups;
+}
+
 // The workgroups count their non-finite outputs as long as there are few
 // enough of them for the caller to add up (8192 events; beyond, the separate
 // pass is under 2 % of the call).
 template <class PROC, class REC>
 inline hipError_t launch(const Fp64Call& a, hipStream_t s) {
-  const int64_t blocks = (a.nevt + 1) / 2;
-  const bool count = a.nonfinite && blocks <= kNonfiniteBlocks;
-  if (a.counts) *a.counts = count ? int(blocks) : 0;
+  const int64_t all = launch_groups(a.nevt, 0);
+  const bool count = a.nonfinite && all <= kNonfiniteBlocks;
+  if (a.counts) *a.counts = count ? int(all) : 0;
   return with_cards<QcdCard>(a, qcd_card, [&](const auto& cards) {
     typedef std::remove_cv_t<std::remove_reference_t<decltype(cards)>> Cards;
-    hipLaunchKernelGGL((ordered_kernel<PROC, REC, false, Cards>), dim3(unsigned(blocks)), dim3(64), 0, s, a.mom,
-                       a.nevt, cards, a.ncards, a.w_in, a.w_out, a.me_out, static_cast<const int32_t*>(nullptr),
-                       static_cast<const unsigned int*>(nullptr), count ? a.nonfinite : nullptr);
-    return hipGetLastError();
+    hipError_t e = hipSuccess;
+    int64_t groups = 0;
+    for (int64_t first0 = 0; first0 < a.nevt && e == hipSuccess; first0 += 2 * groups) {
+      groups = launch_groups(a.nevt, first0);
+      hipLaunchKernelGGL((ordered_kernel<PROC, REC, false, Cards>), dim3(unsigned(groups)), dim3(64), 0, s, a.mom,
+                         a.nevt, cards, a.ncards, a.w_in, a.w_out, a.me_out, static_cast<const int32_t*>(nullptr),
+                         static_cast<const unsigned int*>(nullptr), count ? a.nonfinite : nullptr, first0);
+      e = hipGetLastError();
+    }
+    return e;
   });
 }
 
@@ -212,7 +229,7 @@ inline hipError_t launch_rows(const double* mom, int64_t nevt, const CardPair* c
   const int64_t pairs = (nevt + 1) / 2;
   hipLaunchKernelGGL((ordered_kernel<PROC, REC, true, PairCards>), dim3(unsigned(pairs < 4096 ? pairs : 4096)),
                      dim3(64), 0, s, mom, nevt, PairCards{cards, ncards}, ncards, w_in, w_out, me_out, rows, nrows,
-                     static_cast<unsigned long long*>(nullptr));
+                     static_cast<unsigned long long*>(nullptr), int64_t(0));
   return hipGetLastError();
 }
 
