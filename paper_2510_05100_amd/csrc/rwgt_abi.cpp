@@ -300,20 +300,23 @@ int ensure_guard(rwgt_ctx* c, int64_t nevt) {
   return RWGT_OK;
 }
 
-// Workspace of the mixed path's wave-per-helicity form (null: not used).
-int ensure_parts(rwgt_ctx* c, int64_t nevt, int ncards, void*& parts) {
-  parts = nullptr;
+// Workspace of the mixed path's wave-per-helicity form, or null: me_kernel
+// gives the same results without it, so where the memory is not there the call
+// goes on.
+void* parts_workspace(rwgt_ctx* c, int64_t nevt, int ncards) {
   const size_t bytes = rwgt::me_parts_bytes(c->def->id, nevt, ncards);
-  if (bytes == 0) return RWGT_OK;
+  if (bytes == 0) return nullptr;
   if (bytes > c->me_parts_cap) {
     if (c->me_parts) { hipStreamSynchronize(c->stream); hipFree(c->me_parts); c->me_parts = nullptr; }
     c->me_parts_cap = 0;
-    const hipError_t e = hipMalloc(&c->me_parts, bytes);
-    if (e != hipSuccess) return c->hip_fail(e, "hipMalloc(helicity parts)");
+    if (hipMalloc(&c->me_parts, bytes) != hipSuccess) {
+      c->me_parts = nullptr;
+      (void)hipGetLastError();                   // or the launches would report it
+      return nullptr;
+    }
     c->me_parts_cap = bytes;
   }
-  parts = c->me_parts;
-  return RWGT_OK;
+  return c->me_parts;
 }
 
 // The pinned card buffer, once the previous upload from it is done.
@@ -397,9 +400,7 @@ int run(rwgt_ctx* c, bool reweight, const double* momenta, int64_t nevt, const d
     }
     return run_fp64(c, a, cards);
   }
-  void* parts = nullptr;
   rc = ensure_buffers(c, nevt, int(cards.size()));
-  if (rc == RWGT_OK) rc = ensure_parts(c, nevt, int(cards.size()), parts);
   if (rc == RWGT_OK) rc = cards_ready(c);
   if (rc != RWGT_OK) return rc;
   std::memcpy(c->hcards, cards.data(), cards.size() * sizeof(CardPair));
@@ -422,11 +423,12 @@ int run(rwgt_ctx* c, bool reweight, const double* momenta, int64_t nevt, const d
       g.nflagged = c->guard_count;
       c->guard_ran = true;
     }
+    void* const parts = parts_workspace(c, nevt, int(cards.size()));   // after what the call cannot do without
     e = rwgt::launch_me_guarded(c->def->id, c->precision, c->soa, momenta, nevt, c->dcards, int(cards.size()), w_in,
                                 w_out, me_out, g, parts, c->stream);
   } else {
     e = rwgt::launch_me(c->def->id, c->precision, c->soa, nevt, c->dcards, int(cards.size()), w_in, w_out, me_out,
-                        parts, c->stream);
+                        parts_workspace(c, nevt, int(cards.size())), c->stream);
   }
   if (e != hipSuccess) return c->hip_fail(e, "matrix-element kernel");
   if (c->profiling) hipEventRecord(c->ev[2], c->stream);
@@ -747,10 +749,8 @@ int rwgt_eval_factored(rwgt_ctx* c, const double* momenta, int64_t nevt, const d
       if (e != hipSuccess) return c->hip_fail(e, "hipMalloc(factor cards)");
       c->fac_cards_cap = int(fc.size());
     }
-    void* parts = nullptr;
     if (!fp64) {
-      rc = ensure_parts(c, nevt, nprobe, parts);
-      if (rc == RWGT_OK) rc = cards_ready(c);
+      rc = cards_ready(c);
       if (rc != RWGT_OK) return rc;
       std::memcpy(c->hcards, probes.data(), probes.size() * sizeof(CardPair));
       rc = upload_cards(c, probes.size() * sizeof(CardPair));
@@ -773,7 +773,7 @@ int rwgt_eval_factored(rwgt_ctx* c, const double* momenta, int64_t nevt, const d
       e = rwgt::launch_ingest(c->def->npart, momenta, c->soa, nevt, c->stream);
       if (e == hipSuccess)
         e = rwgt::launch_me(id, c->precision, c->soa, nevt, c->dcards, nprobe, nullptr, nullptr, c->fac_probe,
-                            parts, c->stream);
+                            parts_workspace(c, nevt, nprobe), c->stream);
     }
     if (e == hipSuccess)
       e = rwgt::launch_factored(ew, c->soa, c->def->npart, nevt, ia, ib, c->fac_probe, o.mz, o.wz, c->fac_cards,
