@@ -1,6 +1,6 @@
 """Mixed-precision calls where the workspace of the wave-per-helicity form
-cannot be had (too little device memory): the kernel without it gives the same
-results, so the call is not refused."""
+cannot be had (a stream capture, too little device memory): the kernel without
+it gives the same results, so the call is not refused."""
 import numpy as np
 import pytest
 
@@ -19,6 +19,36 @@ def _setup(proc, nsets):
     rows[:, 0 if qcd else -2] *= 1.0 + 0.01 * np.arange(1, nsets + 1)
     p = dev(np.tile(synth.events(proc, 1000), (BEYOND // 1000, 1, 1)))
     return torch, orig, rows, p, torch.linspace(0.5, 2.0, BEYOND, dtype=torch.float64, device="cuda")
+
+
+@pytest.mark.parametrize("proc,n", [("uu_eeg", 1000), ("gg_ttgg", 777), ("gg_tttt", 5000)])
+def test_capture_of_a_small_call_after_a_large_one(proc, n):
+    """The large call has allocated every buffer but the workspace; the graph
+    of the small one is replayed between eager calls that allocate and replace
+    it."""
+    torch, orig, rows, p, w = _setup(proc, 2)
+    import paper_2510_05100_amd as rw
+    ps, ws = p[:n].contiguous(), w[:n].contiguous()
+    stream = torch.cuda.Stream()
+    with rw.Reweighter(PROCESS_TEXT[proc], orig.slha(), rw.RWGT_MIXED_FP16) as r:
+        rw.rwgt_set_stream(r.ctx, stream.cuda_stream)
+        torch.cuda.synchronize()
+        big = torch.empty((2, BEYOND), dtype=torch.float64, device="cuda")
+        r.eval(p, w, rows, big)
+        torch.cuda.synchronize()
+        small = torch.zeros((2, n), dtype=torch.float64, device="cuda")
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            r.eval(ps, ws, rows, small)
+        for m in (n, 2 * n, 4 * n):
+            small.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(small, big[:, :n])
+            out = torch.empty((2, m), dtype=torch.float64, device="cuda")
+            r.eval(p[:m].contiguous(), w[:m].contiguous(), rows, out)
+            torch.cuda.synchronize()
+            assert torch.equal(out, big[:, :m])
 
 
 def _fill(torch):
