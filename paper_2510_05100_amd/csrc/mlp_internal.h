@@ -41,6 +41,7 @@ struct rwgt_mlp {
   float *tr_part = nullptr, *tr_zws = nullptr;
   void* tr_rows = nullptr;                                // rows of a training step as matrices
   int64_t tr_rows_bytes = 0;
+  int64_t tr_rows_tiles = -1;                             // row tiles it is used up to (< 0: the rule of train_fused)
   int tr_groups = 0;                                      // workgroup slots allocated
   int64_t tr_pstride = 0;
   // batch workspace
@@ -99,6 +100,11 @@ struct rwgt_mlp {
                    float* heads);
   ~rwgt_mlp();
 };
+
+// Not part of the ABI, for tests and measurements of the two forms: training
+// steps of up to this many row tiles run as two kernels (0: none, < 0: the
+// library's rule).
+extern "C" int rwgt_mlp_train_rows_tiles(rwgt_mlp* m, int64_t tiles);
 
 // Host <-> device copy of the parameters, gradients or Adam moments (which:
 // rwgt_mlp::kCopy*) packed layer by layer as W[out_used][in_used], b[out_used];

@@ -80,7 +80,7 @@ int rwgt_mlp::train_fused(const rwgt::TrainArgs& rows_in, float lr) {
   // (2 KB a row at width 128 and depth 3, 64 MB).  Beyond, the one kernel has a
   // workgroup for every compute unit.  A step of 8192 rows of that network takes
   // 67 us in two kernels and 80 us in one, of 1024 rows 42 and 68.
-  const bool by_rows = tiles <= rwgt::kTrainMaxGroups;
+  const bool by_rows = tiles <= (tr_rows_tiles < 0 ? rwgt::kTrainMaxGroups : tr_rows_tiles);
   if (by_rows) {
     const int64_t bytes = rwgt::train_rows_bytes(width, nh, tiles);
     if (bytes > tr_rows_bytes) {
@@ -165,6 +165,12 @@ int rwgt_mlp::predict_rows(const double* mom, const int32_t* ev, const int32_t* 
 }
 
 extern "C" {
+
+int rwgt_mlp_train_rows_tiles(rwgt_mlp* m, int64_t tiles) {
+  if (!m) return RWGT_EINVAL;
+  m->tr_rows_tiles = std::min<int64_t>(tiles, rwgt::kTrainMaxGroups);
+  return RWGT_OK;
+}
 
 int rwgt_train_order(uint64_t seed, int64_t epoch, int64_t n, int64_t pos0, int64_t count, int64_t* out) {
   if (!out || n < 1 || epoch < 0 || pos0 < 0 || count < 0 || pos0 + count > n) return RWGT_EINVAL;
