@@ -158,6 +158,7 @@ struct AdamStep { int adam; float lr, b1, b2, eps, c1, c2; };   // adam = 0: gra
 int train_tile_rows(int width);
 int64_t train_zws_floats(int width, int nh);
 int64_t train_rows_bytes(int width, int nh, int64_t tiles);
+int train_rows_tiles(int width, int nh);   // row tiles up to which two kernels are the faster form
 hipError_t mlp_train_grads(int width, const TrainArgs& a, hipStream_t s);
 // Per Adam segment: the packed copies of the parameter to refresh (NULL: none).
 // Plain data (copied to LDS by the update kernel); value-initialise on the host.

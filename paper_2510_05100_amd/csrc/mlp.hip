@@ -1369,6 +1369,26 @@ int64_t train_rows_bytes(int width, int nh, int64_t tiles) {
   return 16 * (width == 128 ? RowsLayout<128>(tiles, nh).size() : RowsLayout<256>(tiles, nh).size());
 }
 
+// Where the line between the forms lies: the sums kernel reads 2 KB a row (width
+// 128, depth 3) on 53 workgroups however many rows there are, and the rows
+// kernel takes another turn of the chip every 8192 rows (16,384 with z in
+// memory, which leaves the LDS to two workgroups per compute unit); the one
+// kernel grows by 2.1 us for 1024 rows.  At width 128, us a step on given rows (on
+// the pairs of a grid 3 to 5 us more in either form) in two kernels
+// and in one:
+//   depth 2:  8192 rows 48 / 50,   9216 rows 56 / 52
+//   depth 3: 12,288 rows 67 / 70, 13,312 rows 73 / 72
+//   depth 4: 16,384 rows 86 / 90, 17,408 rows 102 / 92; 5: 100 / 101, 120 / 103;
+//         6: 105 / 110, 129 / 113; 7: 113 / 126, 138 / 129
+//   depth 8: 24,576 rows 150 / 155, 25,600 rows 171 / 157; 9: 160 / 170, 182 / 174
+// At width 256 two kernels are the faster form over the whole range that has a
+// slot for every tile, so that the sums keep the one-kernel order (16,384 rows,
+// depth 2: 106 / 119, depth 4: 136 / 201, depth 9: 363 / 534).
+int train_rows_tiles(int width, int nh) {
+  if (width != 128) return kTrainMaxGroups;
+  return RowsLayout<128>::z_lds(nh) ? (nh < 3 ? 32 * (nh + 1) : 128) : 192;
+}
+
 // A wave's 32 rows x 32 features (element i of lane l: row l % 32, feature
 // acc_feat(0, i, l / 32)) to 16-byte units of operand order; one wave's tile.
 struct Turn { bf16 t[32][40]; };                  // [feature][row], rows of 80 bytes

@@ -103,8 +103,9 @@ struct rwgt_mlp {
 
 // Not part of the ABI, for tests and measurements of the two forms: training
 // steps of up to this many row tiles run as two kernels (0: none, < 0: the
-// library's rule).
+// library's rule, which the second gives for a network of depth hidden layers).
 extern "C" int rwgt_mlp_train_rows_tiles(rwgt_mlp* m, int64_t tiles);
+extern "C" int rwgt_mlp_train_rows_rule(int width, int depth);
 
 // Host <-> device copy of the parameters, gradients or Adam moments (which:
 // rwgt_mlp::kCopy*) packed layer by layer as W[out_used][in_used], b[out_used];

@@ -75,12 +75,7 @@ int rwgt_mlp::train_fused(const rwgt::TrainArgs& rows_in, float lr) {
   if (rows_in.n < 1 || tiles > INT32_MAX) return fail(RWGT_EINVAL, "bad row count");
   const int groups = int(std::min<int64_t>(tiles, rwgt::kTrainMaxGroups));
   const int64_t pstride = (adam_total + 1 + 63) / 64 * 64;
-  // Rows and sums as two kernels while every tile has a slot of its own, so that
-  // the sums' order is the one-kernel form's and the rows' matrices are bounded
-  // (2 KB a row at width 128 and depth 3, 64 MB).  Beyond, the one kernel has a
-  // workgroup for every compute unit.  A step of 8192 rows of that network takes
-  // 67 us in two kernels and 80 us in one, of 1024 rows 42 and 68.
-  const bool by_rows = tiles <= (tr_rows_tiles < 0 ? rwgt::kTrainMaxGroups : tr_rows_tiles);
+  const bool by_rows = tiles <= (tr_rows_tiles < 0 ? rwgt::train_rows_tiles(width, nh) : tr_rows_tiles);
   if (by_rows) {
     const int64_t bytes = rwgt::train_rows_bytes(width, nh, tiles);
     if (bytes > tr_rows_bytes) {
@@ -171,6 +166,8 @@ int rwgt_mlp_train_rows_tiles(rwgt_mlp* m, int64_t tiles) {
   m->tr_rows_tiles = std::min<int64_t>(tiles, rwgt::kTrainMaxGroups);
   return RWGT_OK;
 }
+
+int rwgt_mlp_train_rows_rule(int width, int depth) { return rwgt::train_rows_tiles(width, depth - 1); }
 
 int rwgt_train_order(uint64_t seed, int64_t epoch, int64_t n, int64_t pos0, int64_t count, int64_t* out) {
   if (!out || n < 1 || epoch < 0 || pos0 < 0 || count < 0 || pos0 + count > n) return RWGT_EINVAL;
