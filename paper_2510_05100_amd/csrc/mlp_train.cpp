@@ -66,6 +66,24 @@ int rwgt_mlp::ensure_train(int64_t batch, int64_t probes) {
   return e == hipSuccess ? RWGT_OK : hip_fail(e, "clear training batch");
 }
 
+// Workspace of the two-kernel form of the training step; false where the memory
+// is not there: the one kernel, which gives the same bits, has to do.
+bool rwgt_mlp::rows_workspace(int64_t bytes) {
+  if (bytes <= tr_rows_bytes) return true;
+  hipError_t e = hipStreamSynchronize(stream);
+  if (tr_rows) hipFree(tr_rows);
+  tr_rows = nullptr;
+  tr_rows_bytes = 0;
+  if (e == hipSuccess) e = hipMalloc(&tr_rows, size_t(bytes));
+  if (e == hipSuccess) {
+    tr_rows_bytes = bytes;
+    return true;
+  }
+  tr_rows = nullptr;
+  (void)hipGetLastError();                         // or the launches would report it
+  return false;
+}
+
 int rwgt_mlp::train_fused(const rwgt::TrainArgs& rows_in, float lr) {
   int rc = pack();
   if (rc != RWGT_OK) return rc;
@@ -75,20 +93,10 @@ int rwgt_mlp::train_fused(const rwgt::TrainArgs& rows_in, float lr) {
   if (rows_in.n < 1 || tiles > INT32_MAX) return fail(RWGT_EINVAL, "bad row count");
   const int groups = int(std::min<int64_t>(tiles, rwgt::kTrainMaxGroups));
   const int64_t pstride = (adam_total + 1 + 63) / 64 * 64;
-  const bool by_rows = tiles <= (tr_rows_tiles < 0 ? rwgt::train_rows_tiles(width, nh) : tr_rows_tiles);
-  if (by_rows) {
-    const int64_t bytes = rwgt::train_rows_bytes(width, nh, tiles);
-    if (bytes > tr_rows_bytes) {
-      hipError_t e = hipStreamSynchronize(stream);
-      if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
-      if (tr_rows) hipFree(tr_rows);
-      tr_rows = nullptr;
-      tr_rows_bytes = 0;
-      e = hipMalloc(&tr_rows, size_t(bytes));
-      if (e != hipSuccess) return hip_fail(e, "hipMalloc(training rows)");
-      tr_rows_bytes = bytes;
-    }
-  } else if (groups > tr_groups || pstride != tr_pstride) {
+  const bool one = groups <= tr_groups && pstride == tr_pstride;   // the one kernel's workspace is there
+  const bool by_rows = tiles <= (tr_rows_tiles < 0 ? rwgt::train_rows_tiles(width, nh) : tr_rows_tiles) &&
+                       rows_workspace(rwgt::train_rows_bytes(width, nh, tiles));
+  if (!by_rows && !one) {
     hipError_t e = hipStreamSynchronize(stream);
     if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
     if (tr_part) hipFree(tr_part);
