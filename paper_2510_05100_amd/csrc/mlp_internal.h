@@ -95,7 +95,7 @@ struct rwgt_mlp {
   // one fused step over the rows described by rows_in (x / y, or the pairs
   // of a grid); lr > 0: with the Adam step, else gradients and loss only
   int train_fused(const rwgt::TrainArgs& rows_in, float lr);
-  bool rows_workspace(int64_t bytes);
+  bool rows_workspace(int64_t bytes, bool one);
   // heads (mu_y, s_y) [n][2] of rows (ev, cd), fused kernel or layer by layer
   int predict_rows(const double* mom, const int32_t* ev, const int32_t* cd, const float* cpar, int64_t n,
                    float* heads);

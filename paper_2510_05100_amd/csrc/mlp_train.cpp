@@ -66,22 +66,26 @@ int rwgt_mlp::ensure_train(int64_t batch, int64_t probes) {
   return e == hipSuccess ? RWGT_OK : hip_fail(e, "clear training batch");
 }
 
-// Workspace of the two-kernel form of the training step; false where the memory
-// is not there: the one kernel, which gives the same bits, has to do.
-bool rwgt_mlp::rows_workspace(int64_t bytes) {
-  if (bytes <= tr_rows_bytes) return true;
-  hipError_t e = hipStreamSynchronize(stream);
-  if (tr_rows) hipFree(tr_rows);
-  tr_rows = nullptr;
-  tr_rows_bytes = 0;
-  if (e == hipSuccess) e = hipMalloc(&tr_rows, size_t(bytes));
-  if (e == hipSuccess) {
-    tr_rows_bytes = bytes;
-    return true;
+// Workspace of the two-kernel form of the training step; false where the one
+// kernel, which gives the same bits, has to do: where the memory is not there,
+// and in a stream capture, which an allocation ends.  one: the one kernel's
+// workspace is there; a graph takes it, because steps on more rows replace this
+// one more often.
+bool rwgt_mlp::rows_workspace(int64_t bytes, bool one) {
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  hipError_t e = hipStreamIsCapturing(stream, &capture);
+  const bool captured = e != hipSuccess || capture != hipStreamCaptureStatusNone;
+  if (!captured && bytes > tr_rows_bytes) {
+    e = hipStreamSynchronize(stream);
+    if (tr_rows) hipFree(tr_rows);
+    tr_rows = nullptr;
+    tr_rows_bytes = 0;
+    if (e == hipSuccess) e = hipMalloc(&tr_rows, size_t(bytes));
+    if (e == hipSuccess) tr_rows_bytes = bytes;
+    else tr_rows = nullptr;
   }
-  tr_rows = nullptr;
-  (void)hipGetLastError();                         // or the launches would report it
-  return false;
+  if (e != hipSuccess) (void)hipGetLastError();    // or the launches would report it
+  return bytes <= tr_rows_bytes && !(captured && one);
 }
 
 int rwgt_mlp::train_fused(const rwgt::TrainArgs& rows_in, float lr) {
@@ -95,7 +99,7 @@ int rwgt_mlp::train_fused(const rwgt::TrainArgs& rows_in, float lr) {
   const int64_t pstride = (adam_total + 1 + 63) / 64 * 64;
   const bool one = groups <= tr_groups && pstride == tr_pstride;   // the one kernel's workspace is there
   const bool by_rows = tiles <= (tr_rows_tiles < 0 ? rwgt::train_rows_tiles(width, nh) : tr_rows_tiles) &&
-                       rows_workspace(rwgt::train_rows_bytes(width, nh, tiles));
+                       rows_workspace(rwgt::train_rows_bytes(width, nh, tiles), one);
   if (!by_rows && !one) {
     hipError_t e = hipStreamSynchronize(stream);
     if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
