@@ -361,7 +361,10 @@ int run_fp64(rwgt_ctx* c, rwgt::Fp64Call& a, const std::vector<CardPair>& cards)
   if (c->profiling) hipEventRecord(c->ev[0], c->stream);
   if (c->profiling) hipEventRecord(c->ev[1], c->stream);
   const hipError_t e = rwgt::launch_fp64(c->def->id, a, c->stream);
-  if (e != hipSuccess) return c->hip_fail(e, "matrix-element kernel");
+  if (e != hipSuccess) {
+    c->nf_blocks = 0;                            // nothing counted
+    return c->hip_fail(e, "matrix-element kernel");
+  }
   if (c->profiling) hipEventRecord(c->ev[2], c->stream);
   return RWGT_OK;
 }
