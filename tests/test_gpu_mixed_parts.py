@@ -52,3 +52,37 @@ def test_small_calls_equal_large_ones(proc, precision):
                 k = torch.empty(n, dtype=torch.float64, device="cuda")
                 rw.rwgt_cancellation(r.ctx, p[:n].contiguous(), rows, k)
                 assert rel_err(k.cpu().numpy(), big_kappa[:n].cpu().numpy()).max() <= 1e-15
+
+
+@pytest.mark.parametrize("precision", ["RWGT_MIXED_FP16", "RWGT_MIXED_BF16"])
+@pytest.mark.parametrize("proc,sizes", [("ee_mumu", (32_769,)), ("uu_eeg", (16_385, 77_777)),
+                                        ("gg_ttgg", (4097, 20_011)), ("gg_tttt", (4097, 20_011))])
+def test_a_wave_for_all_cards_equals_large_calls(proc, sizes, precision):
+    """From two waves per SIMD on, a wave takes every card in turn instead of
+    one: the first size that does, and a ragged one, bit for bit."""
+    import paper_2510_05100_amd as rw
+    torch = torch_cuda()
+    qcd = proc.startswith("gg")
+    orig = synth.ORIG_QCD if qcd else synth.ORIG_EW
+    rows = np.tile(np.asarray(orig.row(proc), dtype=np.float64), (4, 1))
+    rows[:, 0 if qcd else -2] *= 1.0 + 0.01 * np.arange(1, 5)
+    p = dev(np.tile(synth.events(proc, 1000), (BEYOND // 1000 + 1, 1, 1))[:BEYOND])
+    w = torch.linspace(0.5, 2.0, BEYOND, dtype=torch.float64, device="cuda")
+    with rw.Reweighter(TEXT[proc], orig.slha(), getattr(rw, precision)) as r:
+        for guard in (0.0, 30.0):
+            rw.rwgt_set_mixed_guard(r.ctx, guard)
+            big, big_me = (torch.empty((4, BEYOND), dtype=torch.float64, device="cuda") for _ in range(2))
+            big_kappa = torch.empty(BEYOND, dtype=torch.float64, device="cuda")
+            r.eval(p, w, rows, big)
+            r.me2(p, rows, big_me)
+            rw.rwgt_cancellation(r.ctx, p, rows, big_kappa)
+            for n in sizes:
+                ps, out = p[:n].contiguous(), torch.full((4 * n + 5,), -3.0, dtype=torch.float64, device="cuda")
+                r.eval(ps, w[:n].contiguous(), rows, out[:4 * n])
+                assert torch.equal(out[:4 * n].view(4, n), big[:, :n])
+                assert bool((out[4 * n:] == -3.0).all())
+                r.me2(ps, rows, out[:4 * n])
+                assert torch.equal(out[:4 * n].view(4, n), big_me[:, :n])
+                k = torch.empty(n, dtype=torch.float64, device="cuda")
+                rw.rwgt_cancellation(r.ctx, ps, rows, k)
+                assert torch.equal(k, big_kappa[:n])
