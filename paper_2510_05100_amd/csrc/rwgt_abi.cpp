@@ -1220,14 +1220,18 @@ std::string tune_cache_path() {
 
 // Key of a tuned schedule: the target, the HIP runtime version (a new ROCm
 // may schedule the same kernels differently), the family, precision, segment
-// count and event count (log2).
+// count and event count (log2), and in double precision the kernel's revision:
+// an entry of a kernel that was tuned to other tiles does not fit its
+// successor.  (The single-precision kernels are those of the entries without.)
+constexpr int kBatchFp64Revision = 2;    // 2: tiles dealt out to waves
 std::string tune_key(const rwgt_batch* b, int nseg, int64_t events) {
   int lg = 0;
   while ((int64_t(1) << (lg + 1)) <= events) ++lg;
   int rt = 0;
   if (hipRuntimeGetVersion(&rt) != hipSuccess) rt = 0;
   return "gfx950 hip=" + std::to_string(rt) + " family=" + std::to_string(b->family) +
-         " prec=" + std::to_string(b->precision) + " nseg=" + std::to_string(nseg) + " log2events=" + std::to_string(lg);
+         " prec=" + std::to_string(b->precision) + " nseg=" + std::to_string(nseg) + " log2events=" + std::to_string(lg) +
+         (b->precision == rwgt::kPrecFP64 ? " kernel=" + std::to_string(kBatchFp64Revision) : "");
 }
 
 bool tune_lookup(const std::string& key, rwgt::BatchSchedule& out) {
