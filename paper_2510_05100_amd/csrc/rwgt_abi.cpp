@@ -1454,10 +1454,10 @@ int rwgt_batch_time(rwgt_batch* b, float* ms) {
   return RWGT_OK;
 }
 
-// Grid search over (tile events, workgroup size, workgroups per CU, helicity
-// split) on the given segments, timing each candidate with HIP events; the
-// fastest is kept and appended to the tuning cache (RWGT_TUNE_CACHE, default
-// ~/.rwgt_autotune).
+// Grid search over (tile events, workgroup size, workgroups per CU and, in
+// single precision, helicity split) on the given segments, timing each
+// candidate with HIP events; the fastest is kept and appended to the tuning
+// cache (RWGT_TUNE_CACHE, default ~/.rwgt_autotune).
 int rwgt_batch_tune(rwgt_batch* b, const rwgt_segment* segs, int32_t nseg, int32_t reps) {
   if (!b || !segs || nseg < 1) return RWGT_EINVAL;
   if (reps < 1) reps = 2;
@@ -1468,11 +1468,12 @@ int rwgt_batch_tune(rwgt_batch* b, const rwgt_segment* segs, int32_t nseg, int32
   rwgt::BatchSchedule best_s = b->sched;
   int64_t total = 0;
   for (int32_t k = 0; k < nseg; ++k) total += segs[k].nevt > 0 ? segs[k].nevt : 0;
-  for (int hs = 0; hs <= 1; ++hs)
+  const bool f64 = b->precision == rwgt::kPrecFP64;   // one kernel for both settings of the split, tiles per wave
+  for (int hs = 0; hs <= (f64 ? 0 : 1); ++hs)
     for (int t : tiles)
       for (int bl : blocks)
         for (int pc : per_cu) {
-          if (!hs && bl > t) continue;             // more lanes than the tile's events
+          if (!f64 && !hs && bl > t) continue;     // more lanes than the tile's events
           b->sched = rwgt::BatchSchedule{t, bl, pc * b->ncu, hs};
           b->tuned = true;
           float acc = 0.0f;

@@ -38,6 +38,7 @@ def test_entries_of_another_kernel(tmp_path, monkeypatch, precision, old_entry_u
             rw.rwgt_batch_destroy(b)
     try:
         tuned = schedule()
+        assert precision or tuned["hel_split"] == 0   # one kernel for both settings: not searched
         key = cache.read_text().split("|")[0]
         assert schedule() == tuned               # its own entry
         cache.write_text(f"{key}|{TUNED}\n")
