@@ -93,16 +93,5 @@ __host__ __device__ __forceinline__ R colour_sum(const J& jamp) {
     me += jamp[0].re * zr + jamp[0].im * zi; }
   return me * R(1.0 / 1.0);
 }
-
-// The same from the flows' sums and differences (in place), in which the colour
-// matrix is nearly block diagonal.
-template <class R, class J>
-__host__ __device__ __forceinline__ R colour_sum_paired(J& jamp) {
-  R me = R(0);
-  { const R zr = R(4) * jamp[0].re;
-    const R zi = R(4) * jamp[0].im;
-    me += jamp[0].re * zr + jamp[0].im * zi; }
-  return me * R(1.0 / 1.0);
-}
 }  // namespace gen_uu_eeg
 }  // namespace rwgt

@@ -139,7 +139,6 @@ template <class R> RWGT_HD cx<R> dot(const Spinor<R>& r, const Spinor<R>& c) {
   for (int i = 1; i < 4; ++i) mac(s, r.c[i], c.c[i]);
   return s;
 }
-template <class R> RWGT_HD Spinor<R> operator-(const Spinor<R>& a) { return {{-a.c[0], -a.c[1], -a.c[2], -a.c[3]}}; }
 
 // Coefficients of V-slash between a row and a column: row V-slash col =
 // u w.u + d w.d + p w.p + m w.m.

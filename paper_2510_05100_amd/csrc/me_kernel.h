@@ -15,7 +15,8 @@
 
 namespace rwgt {
 
-#define RWGT_PROCESS_TRAITS(NAME)                                                              \
+// ...: more members (RWGT_PAIRED_COLOUR for a process of several flows).
+#define RWGT_PROCESS_TRAITS(NAME, ...)                                                         \
   struct Proc_##NAME {                                                                         \
     static constexpr int NPART = gen_##NAME::NPART;                                            \
     static constexpr int NCOL = gen_##NAME::NCOL;                                              \
@@ -35,11 +36,13 @@ namespace rwgt {
     static __device__ __forceinline__ R colour_sum(const J& j) {                               \
       return gen_##NAME::colour_sum<R>(j);                                                     \
     }                                                                                          \
-    template <class R, class J>                                                                \
-    static __device__ __forceinline__ R colour_sum_paired(J& j) {                              \
-      return gen_##NAME::colour_sum_paired<R>(j);                                              \
-    }                                                                                          \
+    __VA_ARGS__                                                                                \
   };
+#define RWGT_PAIRED_COLOUR(NAME)                                                               \
+  template <class R, class J>                                                                  \
+  static __device__ __forceinline__ R colour_sum_paired(J& j) {                                \
+    return gen_##NAME::colour_sum_paired<R>(j);                                                \
+  }
 
 template <class R> __device__ __forceinline__ const Card<R>& pick(const CardPair& c);
 template <> __device__ __forceinline__ const Card<double>& pick<double>(const CardPair& c) { return c.d; }

@@ -146,7 +146,7 @@ template <class R, class M> RWGT_HD Lc<R> four_task(M& m, int n, int cfg, R g3, 
 }
 
 // ------------------------------------------------------------ the quark line
-constexpr int kSingleTasks = 14, kHalfSmall = 24, kHalfLarge = 48;   // half tasks of pairs with and without gluon 0
+constexpr int kSingleTasks = 14, kHalfSmall = 24;   // half tasks of pairs with gluon 0 (48 more without)
 
 template <class R> struct Quarks { LcK<R> pt, ptb; R m; };
 

@@ -6,7 +6,7 @@
 
 namespace rwgt {
 
-RWGT_PROCESS_TRAITS(gg_ttgg)
+RWGT_PROCESS_TRAITS(gg_ttgg, RWGT_PAIRED_COLOUR(gg_ttgg))
 
 hipError_t launch_ordered_gg_ttgg(const Fp64Call& a, hipStream_t s) {
   return ordered::launch<Proc_gg_ttgg, ordered::QuarkLine>(a, s);

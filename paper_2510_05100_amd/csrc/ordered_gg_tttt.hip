@@ -6,7 +6,7 @@
 
 namespace rwgt {
 
-RWGT_PROCESS_TRAITS(gg_tttt)
+RWGT_PROCESS_TRAITS(gg_tttt, RWGT_PAIRED_COLOUR(gg_tttt))
 
 hipError_t launch_ordered_gg_tttt(const Fp64Call& a, hipStream_t s) {
   return ordered::launch<Proc_gg_tttt, ordered::QuarkPairs>(a, s);

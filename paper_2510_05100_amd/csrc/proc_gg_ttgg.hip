@@ -5,7 +5,7 @@
 
 namespace rwgt {
 
-RWGT_PROCESS_TRAITS(gg_ttgg)
+RWGT_PROCESS_TRAITS(gg_ttgg, RWGT_PAIRED_COLOUR(gg_ttgg))
 
 hipError_t launch_fp64_gg_ttgg(const Fp64Call& a, hipStream_t s) { return launch_ordered_gg_ttgg(a, s); }
 size_t fp64_table_gg_ttgg(const CardPair* cards, int n, void* out) { return qcd_table(cards, n, out); }

@@ -5,7 +5,7 @@
 
 namespace rwgt {
 
-RWGT_PROCESS_TRAITS(gg_tttt)
+RWGT_PROCESS_TRAITS(gg_tttt, RWGT_PAIRED_COLOUR(gg_tttt))
 
 hipError_t launch_fp64_gg_tttt(const Fp64Call& a, hipStream_t s) { return launch_ordered_gg_tttt(a, s); }
 size_t fp64_table_gg_tttt(const CardPair* cards, int n, void* out) { return qcd_table(cards, n, out); }

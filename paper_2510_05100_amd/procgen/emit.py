@@ -389,7 +389,7 @@ def paired_colour_sum(d: Diagrams, num):
     """Pairs and form of the fewest operations among up to two commuting involutions."""
     n = len(num)
     best = None
-    found = flow_involutions(d, num) if n > 1 else []
+    found = flow_involutions(d, num)
     for chosen in itertools.chain([()], ((f,) for f in found), itertools.permutations(found, 2)):
         if len(chosen) == 2 and any(chosen[0][chosen[1][i]] != chosen[1][chosen[0][i]] for i in range(n)):
             continue
@@ -701,27 +701,28 @@ def generate(d: Diagrams) -> str:
         out.append(f"    me += jamp[{i}].re * zr + jamp[{i}].im * zi; }}")
     out.append(f"  return me * R(1.0 / {den}.0);")
     out.append("}")
-    # the same after sums and differences of flows that the colour matrix does not tell apart
-    pairs, form = paired_colour_sum(d, num)
-    scale = math.lcm(*(x.denominator for row in form for x in row))
-    out.append("")
-    out.append("// The same from the flows' sums and differences (in place), in which the colour")
-    out.append("// matrix is nearly block diagonal.")
-    out.append("template <class R, class J>")
-    out.append("__host__ __device__ __forceinline__ R colour_sum_paired(J& jamp) {")
-    for i, j in pairs:
-        out.append(f"  {{ const cx<R> t = jamp[{i}] + jamp[{j}]; jamp[{j}] = jamp[{i}] - jamp[{j}]; jamp[{i}] = t; }}")
-    out.append("  R me = R(0);")
-    for i in range(ncol):
-        c = [(j, int(form[i][j] * scale) * (1 if i == j else 2)) for j in range(i, ncol) if form[i][j]]
-        if not c:
-            continue
-        for part in ("re", "im"):
-            out.append(f"  {'{ ' if part == 're' else '  '}const R z{part[0]} = "
-                       + " + ".join(f"R({v}) * jamp[{j}].{part}" for j, v in c) + ";")
-        out.append(f"    me += jamp[{i}].re * zr + jamp[{i}].im * zi; }}")
-    out.append(f"  return me * R(1.0 / {den * scale}.0);")
-    out.append("}")
+    if ncol > 1:
+        # the same after sums and differences of flows that the colour matrix does not tell apart
+        pairs, form = paired_colour_sum(d, num)
+        scale = math.lcm(*(x.denominator for row in form for x in row))
+        out.append("")
+        out.append("// The same from the flows' sums and differences (in place), in which the colour")
+        out.append("// matrix is nearly block diagonal.")
+        out.append("template <class R, class J>")
+        out.append("__host__ __device__ __forceinline__ R colour_sum_paired(J& jamp) {")
+        for i, j in pairs:
+            out.append(f"  {{ const cx<R> t = jamp[{i}] + jamp[{j}]; jamp[{j}] = jamp[{i}] - jamp[{j}]; jamp[{i}] = t; }}")
+        out.append("  R me = R(0);")
+        for i in range(ncol):
+            c = [(j, int(form[i][j] * scale) * (1 if i == j else 2)) for j in range(i, ncol) if form[i][j]]
+            if not c:
+                continue
+            for part in ("re", "im"):
+                out.append(f"  {'{ ' if part == 're' else '  '}const R z{part[0]} = "
+                           + " + ".join(f"R({v}) * jamp[{j}].{part}" for j, v in c) + ";")
+            out.append(f"    me += jamp[{i}].re * zr + jamp[{i}].im * zi; }}")
+        out.append(f"  return me * R(1.0 / {den * scale}.0);")
+        out.append("}")
     out.append(f"}}  // namespace gen_{name}")
     out.append("}  // namespace rwgt")
     return "\n".join(out) + "\n"
