@@ -323,17 +323,27 @@ __global__ __launch_bounds__(256) void me_join_kernel(const MePart* __restrict__
   }
 }
 
-// Bytes of the parts, 0: me_kernel itself.  Many-flow kernels hold a SIMD each:
-// from 10 rounds of me_kernel's waves on, the last one costs under 5 %.
-// Few-flow kernels fit several waves on a SIMD and fill the chip at 4096; the
-// join is one launch more (6 us), which fewer than 16 amplitudes in sequence do
-// not repay (e+ e- -> mu+ mu- under two cards has 8: 51 us as it is, 57 split;
-// u u~ -> e+ e- g has 16: 84 and 53).
+// Bytes of the parts, 0: me_kernel itself (also where the caller has no such
+// workspace).  me_kernel's time goes in rounds of 1024 waves, one per SIMD; the
+// parts' with the events, but 4 % (g g -> t t~ g g) to 5.5 % (g g -> t t~ t t~,
+// BF16) above full rounds.  So many-flow processes take them while the last
+// round leaves more than that idle, up to 10 rounds: one new card, ms with and
+// without, 91,750 events (2.8 rounds) 4.60 and 4.73 (g g -> t t~ t t~: 3.02 and
+// 3.08), 98,304 (3) 4.90 and 4.74 (3.22 and 3.09), 188,000 to 196,608 events
+// (5.7 to 6) 1.00 to 1.04 times as long.
+// Few-flow kernels fit several waves on a SIMD: a round adds to the time of one
+// (u u~ -> e+ e- g, one new card: 68 us and 34 for each further one), and the
+// parts are 10 % above full rounds from the third on: 180,224 events (2.75
+// rounds) 133 and 135 us, 196,608 (3) 144 and 135, 229,376 (3.5) 165 and 169,
+// 262,144 (4) 188 and 171.  The join is one launch more (6 us), which fewer than
+// 16 amplitudes in sequence do not repay (e+ e- -> mu+ mu- under two cards has 8:
+// 51 us as it is, 57 split; u u~ -> e+ e- g has 16: 84 and 53).
 template <class PROC>
 inline size_t me_parts_t(int64_t nevt, int ncards) {
   constexpr bool many = hel_split<PROC>() > 1;
-  const int64_t waves = (nevt + 63) / 64 * hel_split<PROC>();
+  const int64_t waves = (nevt + 63) / 64 * hel_split<PROC>(), full = (waves + 1023) / 1024 * 1024;
   if (waves > (many ? 10240 : 4096) || (!many && int64_t(PROC::NSUM) * ncards < 16)) return 0;
+  if (many ? 19 * waves >= 18 * full : full > 2048 && 11 * waves >= 10 * full) return 0;
   const int64_t each = int64_t(sizeof(MePart)) * PROC::NSUM * nevt;
   return ncards <= kPartBytes / each ? size_t(each * ncards) : 0;
 }
