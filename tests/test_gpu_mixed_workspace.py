@@ -53,14 +53,14 @@ def test_capture_of_a_small_call_after_a_large_one(proc, n):
 
 def _fill(torch):
     """Allocations that leave 128 to 256 MB of device memory."""
-    held = []
+    spare, held = torch.empty(128 << 20, dtype=torch.uint8, device="cuda"), []
     for size in (32 << 30, 4 << 30, 512 << 20, 128 << 20):
         while True:
             try:
                 held.append(torch.empty(size, dtype=torch.uint8, device="cuda"))
             except torch.OutOfMemoryError:
                 break
-    held.pop()
+    del spare
     torch.cuda.empty_cache()
     return held
 
