@@ -9,6 +9,18 @@
 
 #include "mlp.h"
 
+namespace rwgt {
+// Whether the stream is being captured (or cannot tell).  The null stream never
+// is; the runtime takes 0.3 us to say so.
+inline bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (!s) return false;
+  if (hipStreamIsCapturing(s, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();                       // or the launches would report it
+  return true;
+}
+}  // namespace rwgt
+
 struct rwgt_mlp {
   enum { kCopyParams = 0, kCopyGrads = 1, kCopyFirst = 2, kCopySecond = 3 };   // pack_params selections
   struct Layer {

@@ -72,20 +72,20 @@ int rwgt_mlp::ensure_train(int64_t batch, int64_t probes) {
 // workspace is there; a graph takes it, because steps on more rows replace this
 // one more often.
 bool rwgt_mlp::rows_workspace(int64_t bytes, bool one) {
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  hipError_t e = hipStreamIsCapturing(stream, &capture);
-  const bool captured = e != hipSuccess || capture != hipStreamCaptureStatusNone;
-  if (!captured && bytes > tr_rows_bytes) {
-    e = hipStreamSynchronize(stream);
-    if (tr_rows) hipFree(tr_rows);
-    tr_rows = nullptr;
-    tr_rows_bytes = 0;
-    if (e == hipSuccess) e = hipMalloc(&tr_rows, size_t(bytes));
-    if (e == hipSuccess) tr_rows_bytes = bytes;
-    else tr_rows = nullptr;
+  if (rwgt::capturing(stream)) return bytes <= tr_rows_bytes && !one;
+  if (bytes <= tr_rows_bytes) return true;
+  hipError_t e = hipStreamSynchronize(stream);
+  if (tr_rows) hipFree(tr_rows);
+  tr_rows = nullptr;
+  tr_rows_bytes = 0;
+  if (e == hipSuccess) e = hipMalloc(&tr_rows, size_t(bytes));
+  if (e == hipSuccess) {
+    tr_rows_bytes = bytes;
+    return true;
   }
-  if (e != hipSuccess) (void)hipGetLastError();    // or the launches would report it
-  return bytes <= tr_rows_bytes && !(captured && one);
+  tr_rows = nullptr;
+  (void)hipGetLastError();                         // or the launches would report it
+  return false;
 }
 
 int rwgt_mlp::train_fused(const rwgt::TrainArgs& rows_in, float lr) {

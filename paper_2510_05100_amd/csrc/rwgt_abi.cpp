@@ -307,18 +307,18 @@ int ensure_guard(rwgt_ctx* c, int64_t nevt) {
 // that a later call may replace.
 void* parts_workspace(rwgt_ctx* c, int64_t nevt, int ncards) {
   const size_t bytes = rwgt::me_parts_bytes(c->def->id, nevt, ncards);
-  if (bytes == 0) return nullptr;
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  hipError_t e = hipStreamIsCapturing(c->stream, &capture);
-  if (e == hipSuccess && capture == hipStreamCaptureStatusNone && bytes > c->me_parts_cap) {
+  if (bytes == 0 || rwgt::capturing(c->stream)) return nullptr;
+  if (bytes > c->me_parts_cap) {
     if (c->me_parts) { hipStreamSynchronize(c->stream); hipFree(c->me_parts); c->me_parts = nullptr; }
     c->me_parts_cap = 0;
-    e = hipMalloc(&c->me_parts, bytes);
-    if (e == hipSuccess) c->me_parts_cap = bytes;
-    else c->me_parts = nullptr;
+    if (hipMalloc(&c->me_parts, bytes) != hipSuccess) {
+      c->me_parts = nullptr;
+      (void)hipGetLastError();                   // or the launches would report it
+      return nullptr;
+    }
+    c->me_parts_cap = bytes;
   }
-  if (e != hipSuccess) (void)hipGetLastError();    // or the launches would report it
-  return e == hipSuccess && capture == hipStreamCaptureStatusNone ? c->me_parts : nullptr;
+  return c->me_parts;
 }
 
 // The pinned card buffer, once the previous upload from it is done.
