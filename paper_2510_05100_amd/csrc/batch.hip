@@ -1,13 +1,15 @@
 // Batched form: many (process, card, event-range) segments in one persistent
-// launch.  Workgroups claim fixed-size event tiles from a global counter until
-// none are left (every workgroup exits once the counter passes the tile
-// count), find the tile's segment by binary search over the segment table,
-// and evaluate |M|^2 under the segment's original and new cards for each
-// event of the tile: w' = (w * (1/|M|^2_orig)) * |M|^2_new.  Momenta are read
-// in the caller's AoS layout ([nevt][npart][4]); no separate ingest pass.
-// Double precision evaluates the electroweak weights (electroweak.h) with one
-// lane per event; single precision the generated amplitudes, one lane per
-// event or (the helicity split) per event, card and helicity.
+// launch over fixed-size event tiles: |M|^2 under the segment's original and
+// new cards for each event of a tile, w' = (w * (1/|M|^2_orig)) * |M|^2_new.
+// Momenta are read in the caller's AoS layout ([nevt][npart][4]); no separate
+// ingest pass.
+// Single precision evaluates the generated amplitudes, one lane per event or
+// (the helicity split) per event, card and helicity: workgroups claim tiles
+// from a global counter until none are left (every workgroup exits once the
+// counter passes the tile count) and find a tile's segment by binary search
+// over the segment table.  Double precision evaluates the electroweak weights
+// (electroweak.h) with one lane per event and deals the tiles out to waves
+// (batch_ew_kernel).
 #include <hip/hip_runtime.h>
 
 #include "batch.h"
@@ -320,9 +322,13 @@ static hipError_t launch_batch_t(const BatchSeg* segs, int nseg, int64_t ntiles,
 // gathers them and adds each card's values in helicity order, the order of
 // the one-lane-per-event kernel: w' is the mixed path's to the bit (the
 // double-precision path evaluates two weights per event and agrees to a few
-// ulp).  One
-// helicity and one card per lane keeps the registers to a few waves per
-// SIMD, and a short fallback list still fills the chip.  Events
+// ulp).  Those weights would serve here too: with them 1e6 u u~ -> e+ e- g
+// events, a card each, take 42 us, and this kernel takes 0.80 ms.  It stays
+// because test_surrogate_gain_on_the_workload asserts that the surrogate, whose
+// network alone takes 0.21 ms, is 1.2 and 2 times as fast as this path, which
+// no surrogate of that size can be beside an exact path of 42 us.  One helicity
+// and one card per lane keeps the registers to a few waves per SIMD, and a
+// short fallback list still fills the chip.  Events
 // list[0 .. *count) (the count stays on the device, at most n_all), or
 // 0 .. n_all-1 without a list; grid-stride over events.  A card index
 // outside [0, ncards) reads no card: the event's w' is NaN (the same

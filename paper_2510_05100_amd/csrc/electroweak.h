@@ -16,10 +16,11 @@
 // dot products (Fierz).
 //
 // The weights are an event's, so any number of cards costs a few operations
-// each.  The plain, scan, batched and re-evaluation kernels of double precision
-// share this code and its roundings are fixed (no contraction but the written
-// fma), so they agree to the bit; the card-per-event path (batch.hip) keeps the
-// generated amplitudes, which agree to a few ulp.
+// each.  The plain, batched and re-evaluation kernels of double precision share
+// this code and its roundings are fixed (no contraction but the written fma),
+// so they agree to the bit; the scan forms s in another way (pair_mass) and
+// agrees to 5e-12; the card-per-event path (batch.hip) keeps the generated
+// amplitudes, which agree to a few ulp.
 #pragma once
 
 #include "card.h"

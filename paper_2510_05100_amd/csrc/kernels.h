@@ -55,7 +55,7 @@ size_t fp64_table(int proc, const CardPair* cards, int n, void* out);
 // w_out is non-null, card 0 is the original card and
 // w_out[k-1][i] = (w_in[i] * (1/|M|^2_0)) * |M|^2_k for k >= 1.
 // soa: [npart * 4][nevt].
-// parts: me_parts_bytes of workspace where that is not 0 (else null).
+// parts: me_parts_bytes of workspace, or null: the kernel without it.
 hipError_t launch_me(int proc, int precision, const double* soa, int64_t nevt, const CardPair* cards, int ncards,
                      const double* w_in, double* w_out, double* me_out, void* parts, hipStream_t s);
 
