@@ -162,8 +162,8 @@ __device__ __forceinline__ double two_cards(const ew::Weights& w, const Card<dou
 // to within the two processes' difference, so dealing them out loses under a
 // tile per wave, where claiming them from one counter costs 16 ns each on this
 // chip whoever claims (4.0e6 events in 128 segments: 1050 us with 64-event
-// tiles, 297 us with 256).  Dealt out: 200 us with 256-event tiles, 650 MB, so
-// 3.2 TB/s (the diagrams of every helicity under both cards took 1.6 - 2.0
+// tiles, 297 us with 256).  Dealt out: 186 us with 256-event tiles, 650 MB, so
+// 3.5 TB/s (the diagrams of every helicity under both cards took 1.6 - 2.0
 // ms); two waves per SIMD at least, one took 236 us.
 struct Piece {
   BatchSeg sg;                                 // wave-uniform
